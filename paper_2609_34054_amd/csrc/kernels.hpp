@@ -49,8 +49,9 @@ struct AttnArgs {
   int32_t group;        // n_q / n_kv
   int32_t head_dim;
   int32_t rank;
-  int32_t n_splits;     // decode: KV splits per request
-  int32_t split_tiles;  // decode: KV tiles per split
+  int32_t n_splits;     // splits with room in the workspace per (request, token, head) row
+  int32_t dec_group;    // decode: consecutive requests whose splits cover the same
+                        // ranges (1: each its own); 0: a prefill, whose splits all write
   int32_t pf_splits;    // prefill: KV splits per row tile (1: none)
   int32_t pf_split_tiles;  // prefill: 64-token KV tiles per split
   // Prefill tile cache in the workspace (tc_data == nullptr: off).  The
@@ -70,9 +71,11 @@ int decode_tile_tokens();
 // runs the shared-base kernel: each base tile is read once for all of them.
 bool decode_shares_base(int batch, int64_t kv_req_stride);
 // `cus`: compute units of the device the call runs on; `paged`: the caches
-// are block pools (the plan follows the kernel form the call takes).
+// are block pools (the plan follows the kernel form the call takes).  The
+// plan gives the number of splits; the kernels cut each request's keys in use
+// into at most that many.
 void decode_plan(int64_t s_cap, int batch, int n_kv, int head_dim, int rank, bool shared_base, bool paged, int cus,
-                 int* n_splits, int* split_tiles);
+                 int* n_splits);
 size_t decode_workspace_bytes(int batch, int n_q, int n_splits, int head_dim, int rank);
 hipError_t launch_decode(const AttnArgs& a, hipStream_t stream);
 

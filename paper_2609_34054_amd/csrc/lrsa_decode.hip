@@ -42,6 +42,7 @@ namespace {
 constexpr int TK = 32;        // tokens per KV tile (one LDS table, one barrier)
 constexpr int NSB = TK / 16;  // 16-token sub-blocks per tile
 constexpr float kRescaleLog2 = 8.f;  // lazy-rescale threshold (log2 domain)
+constexpr int kMaxSplits = 1024;     // the merge holds one split per thread
 // Waves per workgroup (one KV head each).  Rank 64 keeps its B_k^T
 // fragments (64 VGPRs) in registers; with V staged in registers that needs
 // one wave per SIMD (the whole register file, architected plus accumulation
@@ -97,6 +98,38 @@ struct Dec {
   static constexpr int NVD = (16 * V_ROW * 2 + 1023) / 1024;
   static constexpr int VST = NVD * 512;
 };
+
+// Keys request r's query may see: t < kv_len (clamped into the buffer) and
+// t <= the query's position.
+__device__ __forceinline__ int visible_keys(const AttnArgs& a, int r) {
+  int64_t kvl = a.kv_len[r];
+  kvl = kvl < 0 ? 0 : (kvl > a.s_cap ? a.s_cap : kvl);
+  const int64_t pos = a.positions[(int64_t)r * a.n_tok];
+  const int64_t vis = pos + 1 < kvl ? pos + 1 : kvl;
+  return vis < 0 ? 0 : (int)vis;
+}
+// KV tiles per split over `vis` visible keys.  The host plan sizes the grid
+// and the workspace for the caches' capacity (it cannot read kv_len); the
+// splits themselves divide the keys in use, so a cache reserved far beyond
+// its current length still spreads over all the planned workgroups.  Splits
+// at or past the end have no work and write no partial.  (One request, 12345
+// of 65920 tokens, 8 KV heads, rank 16: kernel 31.0 us with splits of the
+// capacity, which leave 43 of 229 workgroups with work, 14.7 us with these.)
+__device__ __forceinline__ int tiles_per_split(int vis, int n_splits) {
+  const int st = ((vis + TK - 1) / TK + n_splits - 1) / n_splits;
+  return st < 1 ? 1 : st;
+}
+// The furthest end among the requests whose splits cover the same ranges
+// (one request, or the dec_group requests of a shared-base workgroup).
+__device__ __forceinline__ int group_visible_keys(const AttnArgs& a, int b, int grp) {
+  const int r0 = b / grp * grp;
+  int vis = visible_keys(a, r0);
+  for (int r = r0 + 1; r < r0 + grp && r < a.batch; ++r) {
+    const int v = visible_keys(a, r);
+    vis = v > vis ? v : vis;
+  }
+  return vis;
+}
 
 // Transposing LDS read: lane j of each 16-lane group points at 4 consecutive
 // bf16; lane i receives element i%4 of lanes i/4, i/4+4, i/4+8, i/4+12.
@@ -247,15 +280,12 @@ lrsa_decode_kernel(const AttnArgs a) {
   bts.issue(has_lk ? a.Bk + (int64_t)b * a.b_stride + (int64_t)g * D : nullptr, (int64_t)a.n_kv * D,
             has_lk && active, lane);
 
-  // Keys this request may see: t < kv_len (clamped into the buffer) and
-  // t <= position of its query token.
-  int64_t kvl = a.kv_len[b];
-  kvl = kvl < 0 ? 0 : (kvl > a.s_cap ? a.s_cap : kvl);
-  const int64_t pos = a.positions[(int64_t)b * a.n_tok];
-  int64_t vis = pos + 1 < kvl ? pos + 1 : kvl;
-  if (vis < 0) vis = 0;
-  const int64_t t_begin = (int64_t)split * a.split_tiles * TK;
-  int64_t t_end = t_begin + (int64_t)a.split_tiles * TK;
+  // This split's share of the keys the request may see.
+  const int vis = visible_keys(a, b);
+  const int st_tiles = tiles_per_split(vis, a.n_splits);
+  const int64_t t_begin = (int64_t)split * st_tiles * TK;
+  if (split > 0 && t_begin >= vis) return;  // past the end (uniform over the workgroup)
+  int64_t t_end = t_begin + (int64_t)st_tiles * TK;
   if (t_end > vis) t_end = vis;
   const int n_tiles = t_end > t_begin ? (int)((t_end - t_begin + TK - 1) / TK) : 0;
 
@@ -530,36 +560,65 @@ tiles_done:
   }
 }
 
+// Splits of request b that wrote partials: decode splits past the request's
+// (shared base: its group's) last key do not exist; a prefill writes them all.
+__device__ __forceinline__ int splits_written(const AttnArgs& a, int b) {
+  if (a.dec_group == 0) return a.n_splits;
+  const int vis = group_visible_keys(a, b, a.dec_group);
+  const int tiles = (vis + TK - 1) / TK, st = tiles_per_split(vis, a.n_splits);
+  const int ns = (tiles + st - 1) / st;
+  return ns < 1 ? 1 : ns;
+}
+
 // Merge the split partials of one (request, query token, q head):
 // log-sum-exp weights, then the deferred up-projection
 // O += (sum_s w_s P_s L_v) B_v, then 1/l.  Decode has one query token per
 // request; a split prefill has n_tok.
 // A row's partials are n_splits x (d + r) fp32 beside their maxima and sums.
-// Thread t owns float4 column t % NV of those d + r accumulators for the
+// Thread s holds split s's maximum and sum (loaded before the number of
+// splits in use is known: that read runs beside it) and leaves its weight in
+// LDS.  Thread t owns float4 column t % NV of the d + r accumulators for the
 // splits congruent to t / NV modulo the number of such groups, so a
 // workgroup keeps one independent 16-byte load per thread and split group
 // in flight; the groups' sums then meet in LDS.  Rows with many splits
 // (small decode batches) take 16-wave workgroups, rows with few 4-wave ones.
+// The chain of dependent reads bounds it: the up-projection column of each
+// output dim is read at the start, beside the partials.
 template <int D, int R, int MW>
 __global__ void __launch_bounds__(64 * MW)
 lrsa_merge_kernel(const AttnArgs a) {
   constexpr int PS = 4 + D + R, NT = 64 * MW;
   constexpr int NV = (D + R) / 4;  // float4 columns of the accumulators
   constexpr int NG = NT / NV;      // split groups
+  static_assert(NT >= D, "one thread per head dim");
   __shared__ float red[NG][D + R];
   __shared__ float red_w[MW][2];
+  __shared__ float wgt[NT];
   __shared__ float fin[D + R];
   const int h = blockIdx.x, bi = blockIdx.y, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int b = bi / a.n_tok;  // bi = request * n_tok + query token
   const int g = h / a.group;
   const bool has_lv = a.Lv != nullptr;
-  const int ns = a.n_splits;
   const int64_t orow = (int64_t)bi * a.n_q + h;  // (request, token, head) row of O
-  const float* base = a.ws + orow * (int64_t)ns * PS;
+  const float* base = a.ws + orow * (int64_t)a.n_splits * PS;
 
-  // Global maximum over the splits.
-  float M = -INFINITY;
-  for (int s = tid; s < ns; s += NT) M = fmaxf(M, base[(int64_t)s * PS]);
+  // One split per thread (n_splits <= NT by the launch rule).
+  f32x2 ml = {-INFINITY, 0.f};
+  if (tid < a.n_splits) ml = *reinterpret_cast<const f32x2*>(base + (int64_t)tid * PS);
+  uint16_t bv[R];
+  if (has_lv && tid < D) {
+    // B_v [r, n_kv*d]: rank j of this thread's head dim, coalesced over the threads.
+    const uint16_t* bp = a.Bv + (int64_t)b * a.b_stride + (int64_t)g * D + tid;
+    const int64_t ldb = (int64_t)a.n_kv * D;
+#pragma unroll
+    for (int j = 0; j < R; ++j) bv[j] = bp[j * ldb];
+  }
+  const int ns = splits_written(a, b);
+  if (tid >= ns) ml = f32x2{-INFINITY, 0.f};
+
+  // Global maximum over the splits, then each split's weight and the row sum
+  // L = sum_s w_s l_s.
+  float M = ml[0];
 #pragma unroll
   for (int x = 1; x < 64; x <<= 1) M = fmaxf(M, shfl_xor(M, x));
   if (lane == 0) red_w[w][0] = M;
@@ -567,15 +626,13 @@ lrsa_merge_kernel(const AttnArgs a) {
 #pragma unroll
   for (int i = 0; i < MW; ++i) M = fmaxf(M, red_w[i][0]);
   const float Ms = (M == -INFINITY) ? 0.f : M;
-
-  // Row sum L = sum_s w_s l_s.
-  float L = 0.f;
-  for (int s = tid; s < ns; s += NT) {
-    const float* p = base + (int64_t)s * PS;
-    L += fast_exp2(p[0] - Ms) * p[1];
-  }
+  const float w_s = fast_exp2(ml[0] - Ms);
+  wgt[tid] = w_s;
+  float L = w_s * ml[1];
 #pragma unroll
   for (int x = 1; x < 64; x <<= 1) L += shfl_xor(L, x);
+  if (lane == 0) red_w[w][1] = L;
+  __syncthreads();
 
   // Weighted accumulators (d of P V, r of P L_v), one float4 column per thread.
   const int grp = tid / NV, v = tid - grp * NV;
@@ -584,15 +641,13 @@ lrsa_merge_kernel(const AttnArgs a) {
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll 4
     for (int s = grp; s < ns; s += NG) {
-      const float* p = base + (int64_t)s * PS;
-      const float wgt = fast_exp2(p[0] - Ms);
-      const f32x4 x = *reinterpret_cast<const f32x4*>(p + 4 + 4 * v);
+      const f32x4 x = *reinterpret_cast<const f32x4*>(base + (int64_t)s * PS + 4 + 4 * v);
+      const float ww = wgt[s];
 #pragma unroll
-      for (int c = 0; c < 4; ++c) acc[c] += wgt * x[c];
+      for (int c = 0; c < 4; ++c) acc[c] += ww * x[c];
     }
     *reinterpret_cast<f32x4*>(&red[grp][4 * v]) = acc;
   }
-  if (lane == 0) red_w[w][1] = L;
   __syncthreads();
   for (int c = tid; c < D + R; c += NT) {
     float t = 0.f;
@@ -608,17 +663,14 @@ lrsa_merge_kernel(const AttnArgs a) {
   // O = (acc + (sum_s w_s P_s L_v) B_v) / L, one head dim per thread.
   const float inv = L > 0.f ? 1.f / L : 0.f;
   uint16_t* o = a.O + orow * D;
-  for (int dim = tid; dim < D; dim += NT) {
-    float sum = fin[dim];
+  if (tid < D) {
+    float sum = fin[tid];
     if (has_lv) {
-      // B_v [r, n_kv*d]: rank j of this head dim, coalesced over the threads.
-      const int64_t ldb = (int64_t)a.n_kv * D;
-      const uint16_t* bv = a.Bv + (int64_t)b * a.b_stride + (int64_t)g * D + dim;
-#pragma unroll 8
-      for (int j = 0; j < R; ++j) sum += fin[D + j] * __uint_as_float((uint32_t)bv[j * ldb] << 16);
+#pragma unroll
+      for (int j = 0; j < R; ++j) sum += fin[D + j] * __uint_as_float((uint32_t)bv[j] << 16);
     }
     const uint32_t pk = pack_bf16(sum * inv, 0.f);
-    o[dim] = (uint16_t)(pk & 0xffffu);
+    o[tid] = (uint16_t)(pk & 0xffffu);
   }
   if (a.lse != nullptr && tid == 0)
     a.lse[orow] = L > 0.f ? (M + __log2f(L)) * kLn2 : -INFINITY;
@@ -662,29 +714,21 @@ lrsa_decode_shared_kernel(const AttnArgs a) {
   const int G = a.group;
   const int q = lane >> 4, c16 = lane & 15;
   const bool has_lk = a.Lk != nullptr, has_lv = a.Lv != nullptr;
-  const int64_t t_begin = (int64_t)split * a.split_tiles * TK;
-  const int64_t t_cap = t_begin + (int64_t)a.split_tiles * TK;
   // The up-projection rows go out first (see the per-request kernel).
   BtStage<D, R> bts;
   bts.issue(has_lk && active ? a.Bk + (int64_t)b * a.b_stride + (int64_t)g * D : nullptr, (int64_t)a.n_kv * D,
             has_lk && active, lane);
 
-  // Keys request r may see: t < min(kv_len, position + 1), within the split.
-  auto req_end = [&](int r) -> int64_t {
-    int64_t kvl = a.kv_len[r];
-    kvl = kvl < 0 ? 0 : (kvl > a.s_cap ? a.s_cap : kvl);
-    const int64_t pos = a.positions[(int64_t)r * a.n_tok];
-    int64_t vis = pos + 1 < kvl ? pos + 1 : kvl;
-    if (vis < t_begin) vis = t_begin;
-    return vis < t_cap ? vis : t_cap;
-  };
-  const int64_t t_end = active ? req_end(b) : t_begin;
-  // The workgroup walks up to the furthest end among its requests.
-  int64_t t_end_wg = t_begin;
-  for (int r = blockIdx.z * NW; r < blockIdx.z * NW + NW && r < a.batch; ++r) {
-    const int64_t e = req_end(r);
-    t_end_wg = e > t_end_wg ? e : t_end_wg;
-  }
+  // The split's range divides the furthest end among the workgroup's
+  // requests; each request stops at its own.
+  const int vis_wg = group_visible_keys(a, blockIdx.z * NW, NW);
+  const int st_tiles = tiles_per_split(vis_wg, a.n_splits);
+  const int64_t t_begin = (int64_t)split * st_tiles * TK;
+  if (split > 0 && t_begin >= vis_wg) return;  // past the end (uniform over the workgroup)
+  const int64_t t_cap = t_begin + (int64_t)st_tiles * TK;
+  auto clip = [&](int64_t end) { return end < t_begin ? t_begin : (end < t_cap ? end : t_cap); };
+  const int64_t t_end = active ? clip(visible_keys(a, b)) : t_begin;
+  const int64_t t_end_wg = clip(vis_wg);
   const int n_steps = __builtin_amdgcn_readfirstlane((int)((t_end_wg - t_begin + STEP - 1) / STEP));
 
   // RoPE table entries of this thread within a sub-block (token, frequency j),
@@ -951,12 +995,12 @@ __global__ void __launch_bounds__(64 * MR_ROWS) lrsa_merge_rows_kernel(const Att
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int64_t orow = (int64_t)blockIdx.x * MR_ROWS + w;  // (request, token, head) row of O
   if (orow >= n_rows) return;
-  const int ns = a.n_splits;
   const int h = (int)(orow % a.n_q);
   const int b = (int)(orow / a.n_q / a.n_tok);
   const int g = h / a.group;
   const bool has_lv = a.Lv != nullptr;
-  const float* base = a.ws + orow * (int64_t)ns * PS;
+  const float* base = a.ws + orow * (int64_t)a.n_splits * PS;
+  const int ns = splits_written(a, b);
 
   const float m_s = lane < ns ? base[(int64_t)lane * PS] : -INFINITY;
   const float l_s = lane < ns ? base[(int64_t)lane * PS + 1] : 0.f;
@@ -1010,6 +1054,8 @@ hipError_t launch_merge_t(const AttnArgs& a, hipStream_t st) {
     return hipGetLastError();
   }
   const dim3 grid(a.n_q, a.batch * a.n_tok);
+  // The wider merge holds one split per thread (decode_plan keeps n_splits
+  // within 1024); rows of at most 64 splits take four waves.
   if (a.n_splits > 64)
     hipLaunchKernelGGL((lrsa_merge_kernel<D, R, 16>), grid, dim3(64 * 16), 0, st, a);
   else
@@ -1018,7 +1064,8 @@ hipError_t launch_merge_t(const AttnArgs& a, hipStream_t st) {
 }
 
 template <int D, int R>
-hipError_t launch_t(const AttnArgs& a, hipStream_t st) {
+hipError_t launch_t(AttnArgs a, hipStream_t st) {
+  a.dec_group = 1;
   if (a.kv_tbl != nullptr) {
     constexpr int nw = dec_nw(D, R, true);
     const dim3 grid(a.n_splits, (a.n_kv + nw - 1) / nw, a.batch);
@@ -1034,8 +1081,9 @@ hipError_t launch_t(const AttnArgs& a, hipStream_t st) {
 }
 
 template <int D, int R>
-hipError_t launch_shared_t(const AttnArgs& a, hipStream_t st) {
+hipError_t launch_shared_t(AttnArgs a, hipStream_t st) {
   using C = Dec<D, R>;
+  a.dec_group = C::NW;
   const int rg = (a.batch + C::NW - 1) / C::NW;
   hipLaunchKernelGGL((lrsa_decode_shared_kernel<D, R>), dim3(a.n_splits, a.n_kv, rg), dim3(C::NT), 0, st, a);
   hipError_t e = hipGetLastError();
@@ -1072,7 +1120,7 @@ int decode_tile_tokens() { return TK; }
 bool decode_shares_base(int batch, int64_t kv_req_stride) { return batch > 1 && kv_req_stride == 0; }
 
 void decode_plan(int64_t s_cap, int batch, int n_kv, int head_dim, int rank, bool shared_base, bool paged, int cus,
-                 int* n_splits, int* split_tiles) {
+                 int* n_splits) {
   const int64_t tiles = (s_cap + TK - 1) / TK;
   const int nw = dec_waves(rank);
   const int64_t nb = batch > 0 ? batch : 1;
@@ -1084,6 +1132,7 @@ void decode_plan(int64_t s_cap, int batch, int n_kv, int head_dim, int rank, boo
     const int64_t target_wgs = rounds * (cus > 0 ? cus : 1) * 8 / nw;
     int64_t ns = (target_wgs + groups - 1) / groups;
     if (ns < 1) ns = 1;
+    if (ns > kMaxSplits) ns = kMaxSplits;
     if (ns > tiles) ns = tiles > 0 ? tiles : 1;
     int64_t st = (tiles + ns - 1) / ns;
     if (st < 1) st = 1;
@@ -1103,7 +1152,6 @@ void decode_plan(int64_t s_cap, int batch, int n_kv, int head_dim, int rank, boo
   plan(2, &ns, &st);
   if (st < 8 || (!shared_base && dec_vdma(head_dim, rank, paged))) plan(1, &ns, &st);
   *n_splits = (int)ns;
-  *split_tiles = (int)st;
 }
 
 size_t decode_workspace_bytes(int batch, int n_q, int n_splits, int head_dim, int rank) {
