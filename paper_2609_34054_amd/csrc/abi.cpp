@@ -446,10 +446,9 @@ size_t workspace_size(const lrsa_dims* dims, bool paged, bool tile_cache = true)
     // per KV head with an LR rank, the tile cache (room is asked for whenever
     // the rank is one of those, since dims do not say whether the call
     // brings L_k).
-    int splits = 1, split_tiles = 0;
+    int splits = 1;
     const int group = dims->n_q_heads / dims->n_kv_heads;
-    prc::prefill_plan(dims->n_tok, group, dims->n_kv_heads, dims->batch, dims->s_cap, plan_cus(), &splits,
-                      &split_tiles);
+    prc::prefill_plan(dims->n_tok, group, dims->n_kv_heads, dims->batch, dims->s_cap, plan_cus(), &splits);
     const size_t parts =
         prc::prefill_workspace_bytes(dims->batch, dims->n_tok, dims->n_q_heads, splits, dims->head_dim, r);
     if (tile_cache && !paged && rank_ok(dims->rank) &&
@@ -503,7 +502,7 @@ prc_status attention_impl(const char* who, const lrsa_dims* dims, const lrsa_pag
     return launch_status(prc::launch_decode(a, st), what);
   }
   const int plan_cu = plan_cus();
-  prc::prefill_plan(a.n_tok, a.group, a.n_kv, a.batch, a.s_cap, plan_cu, &a.pf_splits, &a.pf_split_tiles);
+  prc::prefill_plan(a.n_tok, a.group, a.n_kv, a.batch, a.s_cap, plan_cu, &a.pf_splits);
   // Split partials first (required when the plan splits), then the tile
   // cache, taken when the workspace has room for it (a smaller or absent
   // workspace only means every workgroup rebuilds every tile).

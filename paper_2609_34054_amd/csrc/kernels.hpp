@@ -53,7 +53,6 @@ struct AttnArgs {
   int32_t dec_group;    // decode: consecutive requests whose splits cover the same
                         // ranges (1: each its own); 0: a prefill, whose splits all write
   int32_t pf_splits;    // prefill: KV splits per row tile (1: none)
-  int32_t pf_split_tiles;  // prefill: 64-token KV tiles per split
   // Prefill tile cache in the workspace (tc_data == nullptr: off).  The
   // rebuilt K rows and V^T fragments of a full 64-token tile, in the LDS
   // layout, in eight 4 KB parts (one per wave), [request][KV head][tile][part],
@@ -86,8 +85,7 @@ hipError_t launch_split_merge(const AttnArgs& a, hipStream_t stream);
 // Prefill (several query tokens per request): causal flash attention.  A
 // call with too few (row tile, KV head, request) units to fill the GPU is
 // also split over the KV tiles, each split writing partials for the merge.
-void prefill_plan(int n_tok, int group, int n_kv, int batch, int64_t s_cap, int cus, int* splits,
-                  int* split_tiles);
+void prefill_plan(int n_tok, int group, int n_kv, int batch, int64_t s_cap, int cus, int* splits);
 size_t prefill_workspace_bytes(int batch, int n_tok, int n_q, int splits, int head_dim, int rank);
 // Whether a prefill call shares rebuilt tiles through the workspace tile
 // cache: contiguous caches, d = 128, rank >= 16 with LR on the keys, and
