@@ -73,8 +73,8 @@ bool decode_shares_base(int batch, int64_t kv_req_stride);
 // are block pools (the plan follows the kernel form the call takes).  The
 // plan gives the number of splits; the kernels cut each request's keys in use
 // into at most that many.
-void decode_plan(int64_t s_cap, int batch, int n_kv, int head_dim, int rank, bool shared_base, bool paged, int cus,
-                 int* n_splits);
+void decode_plan(int64_t s_cap, int batch, int n_kv, int group, int head_dim, int rank, bool shared_base, bool paged,
+                 int cus, int* n_splits);
 size_t decode_workspace_bytes(int batch, int n_q, int n_splits, int head_dim, int rank);
 hipError_t launch_decode(const AttnArgs& a, hipStream_t stream);
 

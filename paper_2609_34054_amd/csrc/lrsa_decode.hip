@@ -120,15 +120,16 @@ __device__ __forceinline__ int tiles_per_split(int vis, int n_splits) {
   return st < 1 ? 1 : st;
 }
 // The furthest end among the requests whose splits cover the same ranges
-// (one request, or the dec_group requests of a shared-base workgroup).
-__device__ __forceinline__ int group_visible_keys(const AttnArgs& a, int b, int grp) {
-  const int r0 = b / grp * grp;
-  int vis = visible_keys(a, r0);
-  for (int r = r0 + 1; r < r0 + grp && r < a.batch; ++r) {
-    const int v = visible_keys(a, r);
-    vis = v > vis ? v : vis;
-  }
-  return vis;
+// (one request, or the dec_group <= 64 requests of a shared-base workgroup).
+// Lane i reads request i's length and position, so the reads run side by side;
+// `mine` receives its visible keys (0 past the group or the batch).
+__device__ __forceinline__ int group_visible_keys(const AttnArgs& a, int b, int grp, int lane, int& mine) {
+  const int r = b / grp * grp + lane;
+  mine = lane < grp && r < a.batch ? visible_keys(a, r) : 0;
+  int vis = mine;
+#pragma unroll
+  for (int x = 1; x < 8; x <<= 1) vis = max(vis, __shfl_xor(vis, x, 64));
+  return __builtin_amdgcn_readfirstlane(vis);
 }
 
 // Transposing LDS read: lane j of each 16-lane group points at 4 consecutive
@@ -564,7 +565,8 @@ tiles_done:
 // (shared base: its group's) last key do not exist; a prefill writes them all.
 __device__ __forceinline__ int splits_written(const AttnArgs& a, int b) {
   if (a.dec_group == 0) return a.n_splits;
-  const int vis = group_visible_keys(a, b, a.dec_group);
+  int mine;
+  const int vis = a.dec_group == 1 ? visible_keys(a, b) : group_visible_keys(a, b, a.dec_group, threadIdx.x & 63, mine);
   const int tiles = (vis + TK - 1) / TK, st = tiles_per_split(vis, a.n_splits);
   const int ns = (tiles + st - 1) / st;
   return ns < 1 ? 1 : ns;
@@ -679,304 +681,408 @@ lrsa_merge_kernel(const AttnArgs a) {
 // ---------------------------------------------------------------------------
 // Decode over one base cache shared by every request (kv_req_stride == 0):
 // several agents' queries over the same trajectory, each with its own LR
-// plane, up-projections, query and position.  One workgroup per (split, KV
-// head, group of NW requests); wave w serves request group*NW + w.  Each
-// 64-token step of the head's K_base/V_base rows is read from memory once,
-// staged in LDS, and used by every wave: base bytes are paid once for all
-// agents, and only the agents' LR rows (a few per cent of the base bytes)
-// are read per request.  One barrier per step; within a step each wave runs
-// the per-request kernel's 16-token sub-block work four times.  The partials
-// go to the same workspace and the same merge.
-template <int D, int R>
-__global__ void __launch_bounds__(dec_waves(R) * 64, dec_waves(R) / 4)
-lrsa_decode_shared_kernel(const AttnArgs a) {
+// plane, up-projections, query and position.  The heads of RPB requests fill
+// the 16 columns of one MFMA result (column c: request c / G, head c % G), so
+// a wave scores, softmaxes and weights each 16-token sub-block of the base
+// once for all of them; only the key expansion RoPE(L_k B_k) and P L_v run
+// per request.
+//
+// One workgroup per (split, KV head, up to sh_groups(R) groups of RPB
+// requests): each group has SH_W / n_grp waves, which take the split's
+// sub-blocks in turn (stream s: sub-blocks s, s + n_str, ...), keep their own
+// running softmax and combine through LDS at the end, so nothing in the loop
+// waits for another wave.  The B_k^T fragments of all the workgroup's requests
+// wait in LDS.  The partials go to the same workspace and the same merge.
+//
+// Eight agents over 32k tokens, 8 KV heads, rank 16: 97 us per call with one
+// request per wave (12 of 16 columns empty, softmax and P V repeated per
+// request), 67 us with four.  What is left is vector work: 510 vector
+// instructions per sub-block of four requests, 336 of them the rotation of
+// the expansions, at two waves per SIMD half of the cycles.  Measured and no
+// better: two sub-blocks of loads in flight (256 registers; 72 us), base rows
+// shared by the groups through LDS with a barrier per sub-block (75 us,
+// though without key LR, where memory bounds it, 55 -> 48 us), two rounds of
+// workgroups (84 us: the fixed cost of a workgroup, about 8 us of dependent
+// reads at its start and the combine at its end, is paid twice).
+constexpr int SH_W = 8;                                           // waves per workgroup
+constexpr int sh_groups(int rank) { return rank >= 64 ? 1 : 2; }  // request groups per workgroup (B_k in LDS: 64 KB at most)
+// Requests whose heads share the 16 columns; more than 4 would only lengthen
+// the per-request part of a sub-block.
+constexpr int sh_rpb(int group) { return group <= 4 ? 4 : (group == 5 ? 3 : 2); }
+
+template <int D, int R, int RPB>
+__global__ void __launch_bounds__(SH_W * 64, 2)
+lrsa_decode_shared_kernel(const AttnArgs a, int n_grp) {
   using C = Dec<D, R>;
-  constexpr int NW = C::NW, NT = C::NT;
-  constexpr int SB = 16;                    // tokens per sub-block
-  constexpr int NSS = 4;                    // sub-blocks per step
-  constexpr int STEP = SB * NSS;            // tokens per step (one barrier)
-  constexpr int K_ROW = D + 8;              // conflict-free 16-byte row reads
-  constexpr int EPS = SB * C::HALF / NT;    // RoPE table entries per thread per sub-block
-  constexpr int CPR = D / 8;                // 16-byte chunks per base row
-  constexpr int NBC = 2 * STEP * CPR;       // base chunks (K rows, then V rows) per step
-  constexpr int NCK = (NBC + NT - 1) / NT;  // base chunks per thread per step
-  static_assert(EPS >= 1 && SB * C::HALF % NT == 0 && NSS * C::HALF <= NT, "step sizes");
-  __shared__ float2 cs_lds[2][NSS][SB * C::CS_ROW];
-  __shared__ float2 base_lds[2][NSS][C::HALF];
-  __shared__ __attribute__((aligned(16))) uint16_t k_lds[2][STEP * K_ROW];
-  __shared__ __attribute__((aligned(16))) uint16_t v_lds[2][STEP * C::V_ROW];
-  __shared__ __attribute__((aligned(16))) uint16_t lv_lds[NW][16 * C::LV_ROW];
+  using Frag = typename Ex<R>::Frag;
+  constexpr int SB = 16, NTH = SH_W * 64, NC = Ex<R>::NC;
+  constexpr int NBF = C::NBLK * NC * 64;  // B_k^T fragments of one request
+  // LDS: B_k^T fragments, V and L_v tiles, RoPE offsets and base angles; the
+  // streams' partials reuse it after the loop.
+  constexpr int kBk = sh_groups(R) * RPB * NBF * (int)sizeof(Frag);
+  // L_v tiles: one per request up to rank 16, so that all are written with V
+  // at the head of a sub-block; above, one that the requests use in turn.
+  constexpr int NLT = R <= 16 ? RPB : 1, LVT = 16 * C::LV_ROW;
+  constexpr int kV = SH_W * 16 * C::V_ROW * 2, kLv = SH_W * NLT * LVT * 2;
+  constexpr int kOff = SB * C::CS_ROW * 8 + (SB * C::CS_ROW % 2) * 8, kBase = SH_W * 2 * C::HALF * 8;
+  constexpr int kLoop = kBk + kV + kLv + kOff + kBase;
+  constexpr int PR = D + R + 4, kPart = SH_W * 16 * PR * 4;  // [wave][column][acc, accl, m, l]
+  static_assert(kBk % 16 == 0 && kV % 16 == 0 && kLv % 16 == 0 && kOff % 16 == 0, "16-byte aligned areas");
+  __shared__ __attribute__((aligned(16))) char smem[kLoop > kPart ? kLoop : kPart];
+  Frag* bk_lds = reinterpret_cast<Frag*>(smem);
+  float2* off_lds = reinterpret_cast<float2*>(smem + kBk + kV + kLv);
 
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int split = blockIdx.x, g = blockIdx.y;
-  const int b = blockIdx.z * NW + w;
-  const bool active = b < a.batch;
-  const int G = a.group;
+  const int n_str = SH_W / n_grp, grp = w / n_str, stream = w - grp * n_str;
+  const int split = blockIdx.x, g = blockIdx.y, G = a.group;
+  const int b_wg = blockIdx.z * n_grp * RPB, b0 = b_wg + grp * RPB;  // first request of the workgroup, of this wave
   const int q = lane >> 4, c16 = lane & 15;
   const bool has_lk = a.Lk != nullptr, has_lv = a.Lv != nullptr;
-  // The up-projection rows go out first (see the per-request kernel).
-  BtStage<D, R> bts;
-  bts.issue(has_lk && active ? a.Bk + (int64_t)b * a.b_stride + (int64_t)g * D : nullptr, (int64_t)a.n_kv * D,
-            has_lk && active, lane);
-
   // The split's range divides the furthest end among the workgroup's
   // requests; each request stops at its own.
-  const int vis_wg = group_visible_keys(a, blockIdx.z * NW, NW);
-  const int st_tiles = tiles_per_split(vis_wg, a.n_splits);
-  const int64_t t_begin = (int64_t)split * st_tiles * TK;
-  if (split > 0 && t_begin >= vis_wg) return;  // past the end (uniform over the workgroup)
-  const int64_t t_cap = t_begin + (int64_t)st_tiles * TK;
-  auto clip = [&](int64_t end) { return end < t_begin ? t_begin : (end < t_cap ? end : t_cap); };
-  const int64_t t_end = active ? clip(visible_keys(a, b)) : t_begin;
-  const int64_t t_end_wg = clip(vis_wg);
-  const int n_steps = __builtin_amdgcn_readfirstlane((int)((t_end_wg - t_begin + STEP - 1) / STEP));
-
-  // RoPE table entries of this thread within a sub-block (token, frequency j),
-  // and the sub-block base angle it computes (sub-block tid / HALF, j).
-  float cdl[EPS], sdl[EPS];
-  int ej[EPS], eidx[EPS];
+  static_assert(sh_groups(R) * RPB <= 8, "one reduction over 8 lanes");
+  int vis_lane;
+  const int vis_wg = group_visible_keys(a, b_wg, n_grp * RPB, lane, vis_lane);
+  const int st_tiles = __builtin_amdgcn_readfirstlane(tiles_per_split(vis_wg, a.n_splits));
+  if (split > 0 && (int64_t)split * st_tiles * TK >= vis_wg) return;  // past the end (uniform over the workgroup)
+  const int t_begin = split * st_tiles * TK;
+  auto clip = [&](int end) { return end < t_begin ? t_begin : (end - t_begin < st_tiles * TK ? end : t_begin + st_tiles * TK); };
+  const int t_end_wg = __builtin_amdgcn_readfirstlane(clip(vis_wg));
+  int t_end_r[RPB];  // per request of this wave (uniform)
 #pragma unroll
-  for (int k = 0; k < EPS; ++k) {
-    const int e = tid + NT * k, tok = e / C::HALF;
-    ej[k] = e - tok * C::HALF;
-    eidx[k] = tok * C::CS_ROW + ej[k];
-    cdl[k] = 1.f;
-    sdl[k] = 0.f;
-    if (has_lk) rope_cs(tok, a.w2pi[ej[k]], cdl[k], sdl[k]);
+  for (int i = 0; i < RPB; ++i) t_end_r[i] = clip(__builtin_amdgcn_readlane(vis_lane, grp * RPB + i));
+  // This lane's column: request slot, head, end.
+  const int slot = c16 / G, b_l = b0 + slot;
+  const bool col_ok = slot < RPB && b_l < a.batch;
+  int t_end_l = t_begin;
+#pragma unroll
+  for (int i = 0; i < RPB; ++i) t_end_l = slot == i ? t_end_r[i] : t_end_l;
+
+  // Q^T of the columns as the B operand (zero where there is no head).
+  bf16x8 qf[C::NCH];
+  {
+    const uint16_t* qp =
+        a.Q + ((int64_t)(col_ok ? b_l : 0) * a.n_tok * a.n_q + (int64_t)g * G + (col_ok ? c16 - slot * G : 0)) * D;
+#pragma unroll
+    for (int kk = 0; kk < C::NCH; ++kk) qf[kk] = as_bf16x8(ld16(qp + chunk_dim<D>(kk, q), col_ok));
   }
-  const int bsb = tid / C::HALF, bj = tid % C::HALF;  // base angle this thread computes
-  const bool base_thread = has_lk && tid < NSS * C::HALF;
-  const double w2pi_t = a.w2pi[bj];
-  auto base_angles = [&](int64_t t0s, int buf) {
-    if (base_thread) {
-      float c, s;
-      rope_cs((int)(t0s + bsb * SB), w2pi_t, c, s);
-      base_lds[buf][bsb][bj] = make_float2(c, s);
-    }
-  };
-  if (n_steps > 0) base_angles(t_begin, 0);
-  for (int i = lane; i < 16 * C::LV_ROW; i += 64) lv_lds[w][i] = 0;
+
+  const double w2pi_l = a.w2pi[lane % C::HALF];
+
+  // One-time loads first (all of them older than the staged rows, so the
+  // loop's waits count staged loads only): a wave per request reads its B_k.
+  BtStage<D, R> bts;
+  {
+    const bool ok = has_lk && w < n_grp * RPB && b_wg + w < a.batch;
+    bts.issue(ok ? a.Bk + (int64_t)(b_wg + w) * a.b_stride + (int64_t)g * D : nullptr, (int64_t)a.n_kv * D, ok, lane);
+  }
 
   const int64_t row = (int64_t)a.n_kv * D;
   const uint16_t* Kb = a.Kb + (int64_t)g * D;
   const uint16_t* Vb = a.Vb + (int64_t)g * D;
-  const uint16_t* Lk = has_lk && active ? a.Lk + (int64_t)b * a.l_stride : nullptr;
-  const uint16_t* Lv = has_lv && active ? a.Lv + (int64_t)b * a.l_stride : nullptr;
-
-  // Base chunks of a step: chunk c < STEP*CPR is K row c / CPR, else V.
-  int32_t boff[NCK];
+  const int vrow = lane / C::LPR, vdim = (lane % C::LPR) * 8;
+  int32_t voff[C::NVL], lvoff[C::RC], lkoff[NC];
+  const int32_t koff = c16 * (int32_t)(row * 2) + chunk_dim<D>(0, q) * 2;
 #pragma unroll
-  for (int k = 0; k < NCK; ++k) {
-    const int c = (tid + NT * k) % (STEP * CPR);
-    boff[k] = tid + NT * k < NBC ? (c / CPR) * (int32_t)(row * 2) + (c % CPR) * 16 : INT32_MIN;
-  }
-  auto base_load = [&](u32x4 (&r)[NCK], int64_t t0) {
-    const int64_t n = t_end_wg - t0 < 0 ? 0 : (t_end_wg - t0 < STEP ? t_end_wg - t0 : STEP);
-    const int32_t bytes = n > 0 ? (int32_t)((n - 1) * row * 2 + D * 2) : 0;
-    const auto rk = make_rsrc(Kb + t0 * row, bytes), rv = make_rsrc(Vb + t0 * row, bytes);
-#pragma unroll
-    for (int k = 0; k < NCK; ++k) {
-      const bool isk = (tid + NT * k) < STEP * CPR;
-      r[k] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(isk ? rk : rv, boff[k], 0, 0));
-    }
-  };
-  auto base_store = [&](const u32x4 (&r)[NCK], int buf) {
-#pragma unroll
-    for (int k = 0; k < NCK; ++k) {
-      const int c = tid + NT * k, cc = c % (STEP * CPR), tok = cc / CPR, col = (cc % CPR) * 8;
-      if (c < STEP * CPR)
-        *reinterpret_cast<u32x4*>(k_lds[buf] + tok * K_ROW + col) = r[k];
-      else if (c < NBC)
-        *reinterpret_cast<u32x4*>(v_lds[buf] + tok * C::V_ROW + col) = r[k];
-    }
-  };
-  // This wave's LR rows of a sub-block (rank chunks of token l%16), zero past
-  // its end.
-  struct LrStage {
-    typename Ex<R>::Frag lk[Ex<R>::NC];
-    u32x2 lv[C::RC];
-  };
-  int32_t lroff[C::RC], lkoff[Ex<R>::NC];
+  for (int iv = 0; iv < C::NVL; ++iv) voff[iv] = (vrow + C::RPL * iv) * (int32_t)(row * 2) + vdim * 2;
 #pragma unroll
   for (int rc = 0; rc < C::RC; ++rc) {
     const int r0 = rc * 16 + q * 4;
-    lroff[rc] = r0 < R ? c16 * R * 2 + r0 * 2 : INT32_MIN;
+    lvoff[rc] = r0 < R ? c16 * R * 2 + r0 * 2 : INT32_MIN;
   }
 #pragma unroll
-  for (int c = 0; c < Ex<R>::NC; ++c) {
+  for (int c = 0; c < NC; ++c) {
     const int r0 = Ex<R>::rank0(c, q);
     lkoff[c] = r0 < R ? c16 * R * 2 + r0 * 2 : INT32_MIN;
   }
-  auto lr_load = [&](LrStage& s, int64_t t0) {
-    const int64_t n = t_end - t0 < 0 ? 0 : (t_end - t0 < SB ? t_end - t0 : SB);
-    const auto rlk = make_rsrc(Lk != nullptr ? Lk + t0 * R : Kb, Lk != nullptr ? (int32_t)(n * R * 2) : 0);
-    const auto rlv = make_rsrc(Lv != nullptr ? Lv + t0 * R : Kb, Lv != nullptr ? (int32_t)(n * R * 2) : 0);
+  // Staged rows of the next sub-block.  Rows past an end read as zeros and
+  // touch no memory.
+  u32x4 kst[C::NCH], vst[C::NVL];
+  Frag lkst[RPB][NC];
+  u32x2 lvst[RPB][C::RC];
+  // Every path issues the same loads in the same order, without branches, so
+  // that the compiler's load counting waits only for what it needs (a load
+  // behind a branch made each sub-block wait for the last load issued: the
+  // whole memory latency).
+  // (readfirstlane: the clamp would otherwise be done on the vector ALU, and
+  // resources in vector registers cost a loop around each load.)
+  auto valid = [&](int end, int t0) { return __builtin_amdgcn_readfirstlane(max(0, min(end - t0, SB))); };
+  auto load_base = [&](int t0) {
+    const int n = valid(t_end_wg, t0);
+    const int32_t bytes = n > 0 ? (n - 1) * (int32_t)(row * 2) + D * 2 : 0;
+    const auto rk = make_rsrc(Kb + t0 * row, bytes), rv = make_rsrc(Vb + t0 * row, bytes);
 #pragma unroll
-    for (int c = 0; c < Ex<R>::NC; ++c) s.lk[c] = lr_frag_load<R>(rlk, lkoff[c]);
+    for (int kk = 0; kk < C::NCH; ++kk)
+      kst[kk] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rk, koff + chunk_dim<D>(kk, 0) * 2, 0, 0));
 #pragma unroll
-    for (int rc = 0; rc < C::RC; ++rc)
-      s.lv[rc] = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(rlv, lroff[rc], 0, 0));
+    for (int iv = 0; iv < C::NVL; ++iv)
+      vst[iv] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rv, voff[iv], 0, 0));
+  };
+  // Absent LR caches read the base through empty resources: zeros.
+  const uint16_t* Lk = has_lk ? a.Lk + (int64_t)b0 * a.l_stride : Kb;
+  const uint16_t* Lv = has_lv ? a.Lv + (int64_t)b0 * a.l_stride : Kb;
+  const int lk_row = has_lk ? R * 2 : 0, lv_row = has_lv ? R * 2 : 0;
+  auto load_lk = [&](int t0) {
+#pragma unroll
+    for (int i = 0; i < RPB; ++i) {
+      const auto r = make_rsrc(Lk + i * a.l_stride + (int64_t)t0 * R, valid(t_end_r[i], t0) * lk_row);
+#pragma unroll
+      for (int c = 0; c < NC; ++c) lkst[i][c] = lr_frag_load<R>(r, lkoff[c]);
+    }
+  };
+  auto load_lv = [&](int t0) {
+#pragma unroll
+    for (int i = 0; i < RPB; ++i) {
+      const auto r = make_rsrc(Lv + i * a.l_stride + (int64_t)t0 * R, valid(t_end_r[i], t0) * lv_row);
+#pragma unroll
+      for (int rc = 0; rc < C::RC; ++rc)
+        lvst[i][rc] = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(r, lvoff[rc], 0, 0));
+    }
   };
 
-  bf16x8 qf[C::NCH];
-  {
-    const bool ok = active && c16 < G;
-    const uint16_t* qp = a.Q + ((int64_t)(active ? b : 0) * a.n_tok * a.n_q + (int64_t)g * G + c16) * D;
+  const int n_sb = (t_end_wg - t_begin + SB - 1) / SB;
+  load_base(t_begin + stream * SB);
+  load_lk(t_begin + stream * SB);
+  load_lv(t_begin + stream * SB);
+
+  // B_k^T fragments of every request of the workgroup, fragment order: a
+  // wave per request, read with coalesced loads and transposed through its V
+  // tile.
+  if (has_lk) {
+    const int r = w;
+    if (r < n_grp * RPB) {
+      Frag f[C::NBLK][NC];
+      bts.finish(f, reinterpret_cast<uint16_t*>(smem + kBk) + w * 16 * C::V_ROW, lane);
 #pragma unroll
-    for (int kk = 0; kk < C::NCH; ++kk) qf[kk] = as_bf16x8(ld16(qp + chunk_dim<D>(kk, q), ok));
+      for (int blk = 0; blk < C::NBLK; ++blk)
+#pragma unroll
+        for (int c = 0; c < NC; ++c) bk_lds[r * NBF + (blk * NC + c) * 64 + lane] = f[blk][c];
+    }
+    // In-tile offsets of this lane's frequency (read above: a load here would
+    // wait for the staged rows, which were issued before it).
+    constexpr int TPW = 64 / C::HALF;  // tokens per wave and step
+    for (int tok = w * TPW + lane / C::HALF; tok < SB; tok += SH_W * TPW) {
+      float c, s;
+      rope_cs(tok, w2pi_l, c, s);
+      off_lds[tok * C::CS_ROW + lane % C::HALF] = make_float2(c, s);
+    }
   }
-  typename Ex<R>::Frag bkf[C::NBLK][Ex<R>::NC];
-  // Staged through this wave's share of the (not yet used) V tiles.
-  bts.finish(bkf, &v_lds[0][0] + w * 16 * C::V_ROW, lane);
+  uint16_t* vl = reinterpret_cast<uint16_t*>(smem + kBk) + w * 16 * C::V_ROW;
+  uint16_t* lvl = reinterpret_cast<uint16_t*>(smem + kBk + kV) + w * NLT * LVT;
+  float2* base = reinterpret_cast<float2*>(smem + kBk + kV + kLv + kOff) + w * 2 * C::HALF;  // [2][HALF]
+  for (int i = lane; i < NLT * LVT; i += 64) lvl[i] = 0;
 
   float m_run = -INFINITY, l_part = 0.f;
-  f32x4 acc[C::NBLK];
-  f32x4 accl[C::RC];
+  f32x4 acc[C::NBLK], accl[C::RC];
 #pragma unroll
   for (int blk = 0; blk < C::NBLK; ++blk) acc[blk] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int rc = 0; rc < C::RC; ++rc) accl[rc] = f32x4{0.f, 0.f, 0.f, 0.f};
-  uint16_t* lvl = lv_lds[w];
   const int tr_row = 4 * q + (c16 >> 2), tr_col = 4 * (c16 & 3);
 
-  // The base rows of the next step are in flight during a step; the wave's
-  // LR rows run two sub-blocks ahead in a ring of NSS (static indices).
-  u32x4 breg[NCK];
-  LrStage lr[NSS];
-  base_load(breg, t_begin);
-  lr_load(lr[0], t_begin);
-  lr_load(lr[1], t_begin + SB);
-  __syncthreads();  // base angles of the first step, zeroed L_v tiles
+  // Exact angles of a sub-block's first token, a sub-block ahead.
+  auto base_angles = [&](int t0, int buf) {
+    float c, s;
+    rope_cs(t0, w2pi_l, c, s);
+    if (lane < C::HALF) base[buf * C::HALF + lane] = make_float2(c, s);
+  };
+  auto lv_store = [&](int r) {
+#pragma unroll
+    for (int rc = 0; rc < C::RC; ++rc)
+      if (rc * 16 + q * 4 < R)
+        *reinterpret_cast<u32x2*>(lvl + (r % NLT) * LVT + c16 * C::LV_ROW + rc * 16 + q * 4) = lvst[r][rc];
+  };
+  base_angles(t_begin + stream * SB, 0);
+  __syncthreads();  // B_k^T fragments and offsets in LDS
 
-  for (int step = 0; step < n_steps; ++step) {
-    const int buf = step & 1;
-    const int64_t t0s = t_begin + (int64_t)step * STEP;
-    // ---- stage this step (tables, base rows) and start the next one -------
-    if (has_lk) {
+  int buf = 0;
+  for (int sb = stream; sb < n_sb; sb += n_str, buf ^= 1) {
+    const int ts = t_begin + sb * SB, tn = ts + n_str * SB;
+    // The two waves of a SIMD (w, w + 4) take turns at the higher issue
+    // priority: left alone the older one always issues first, finishes early
+    // and leaves the other without a partner (74 -> 71 us).
+    if ((buf ^ (w >> 2)) & 1) __builtin_amdgcn_s_setprio(1);
+    else __builtin_amdgcn_s_setprio(0);
+    // ---- base scores, V (and L_v) rows to LDS; the next sub-block's loads ------
 #pragma unroll
-      for (int sb = 0; sb < NSS; ++sb) {
-        const float2* base = base_lds[buf][sb];
-        float2* cs = cs_lds[buf][sb];
+    for (int iv = 0; iv < C::NVL; ++iv)
+      *reinterpret_cast<u32x4*>(vl + (vrow + C::RPL * iv) * C::V_ROW + vdim) = vst[iv];
+    f32x4 sc0 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int k = 0; k < EPS; ++k) {
-          const float2 bc = base[ej[k]];
-          cs[eidx[k]] = make_float2(bc.x * cdl[k] - bc.y * sdl[k], bc.y * cdl[k] + bc.x * sdl[k]);
-        }
+    for (int kk = 0; kk < C::NCH; ++kk) sc0 = mfma16x16x32(as_bf16x8(kst[kk]), qf[kk], sc0);
+    load_base(tn);
+    if constexpr (NLT == RPB) {
+      if (has_lv) {
+#pragma unroll
+        for (int r = 0; r < RPB; ++r) lv_store(r);
       }
-      if (step + 1 < n_steps) base_angles(t0s + STEP, buf ^ 1);
+      load_lv(tn);
     }
-    base_store(breg, buf);
-    base_load(breg, t0s + STEP);
-    __syncthreads();  // step's tables and base rows visible; double buffers
-                      // keep the previous step's intact for slower waves
-    const uint16_t* kt = k_lds[buf];
-    const uint16_t* vt = v_lds[buf];
+    __builtin_amdgcn_sched_barrier(0);
+    // ---- key expansion of each request, into its columns' scores -------------
+    f32x4 sc = sc0;
+    if (has_lk) {
+      // Two 16-dim blocks of each RoPE half at a time (one 8-dim chunk of the
+      // low half and its partner): the angles of four blocks at once would
+      // cost 16 more registers.
+      f32x4 sr[RPB];
 #pragma unroll
-    for (int sb = 0; sb < NSS; ++sb) {
-      const int64_t ts = t0s + sb * SB;
-      lr_load(lr[(sb + 2) % NSS], ts + 2 * SB);
-      if (!active || ts >= t_end) continue;
-      const LrStage& cur = lr[sb];
-        if (has_lv) {
+      for (int r = 0; r < RPB; ++r) sr[r] = sc0;
 #pragma unroll
-          for (int rc = 0; rc < C::RC; ++rc)
-            if (rc * 16 + q * 4 < R) *reinterpret_cast<u32x2*>(lvl + c16 * C::LV_ROW + rc * 16 + q * 4) = cur.lv[rc];
-        }
-        // ---- scores S^T = K_base Q^T + bf16(RoPE(E)) Q^T --------------------
-        f32x4 sc = {0.f, 0.f, 0.f, 0.f};
+      for (int hb = 0; hb < C::NB / 2; ++hb) {
+        float cc[2][4], ss[2][4];
 #pragma unroll
-        for (int kk = 0; kk < C::NCH; ++kk)
-          sc = mfma16x16x32(as_bf16x8(*reinterpret_cast<const u32x4*>(kt + (sb * SB + c16) * K_ROW + chunk_dim<D>(kk, q))),
-                            qf[kk], sc);
-        if (has_lk) {
-          const float2* csr = cs_lds[buf][sb] + c16 * C::CS_ROW + q * C::QPG;
-          u32x4 ek[C::NCH];
+        for (int b2 = 0; b2 < 2; ++b2)
 #pragma unroll
-          for (int blk = 0; blk < C::NB; ++blk) {
+          for (int i = 0; i < 4; ++i) {
+            const int j = q * C::QPG + (2 * hb + b2) * 4 + i;
+            const float2 o = off_lds[c16 * C::CS_ROW + j], bs = base[buf * C::HALF + j];
+            cc[b2][i] = bs.x * o.x - bs.y * o.y;
+            ss[b2][i] = bs.y * o.x + bs.x * o.y;
+          }
+#pragma unroll
+        for (int r = 0; r < RPB; ++r) {
+          const Frag* bk = bk_lds + (grp * RPB + r) * NBF + lane;
+          u32x4 elc, ehc;  // chunks hb and hb + NB / 2 of the rotated expansion
+#pragma unroll
+          for (int b2 = 0; b2 < 2; ++b2) {
+            const int blk = 2 * hb + b2;
             f32x4 elo = {0.f, 0.f, 0.f, 0.f}, ehi = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int c = 0; c < Ex<R>::NC; ++c) {
-              elo = Ex<R>::mma(bkf[blk][c], cur.lk[c], elo);
-              ehi = Ex<R>::mma(bkf[blk + C::NB][c], cur.lk[c], ehi);
+            for (int c = 0; c < NC; ++c) {
+              elo = Ex<R>::mma(bk[(blk * NC + c) * 64], lkst[r][c], elo);
+              ehi = Ex<R>::mma(bk[((blk + C::NB) * NC + c) * 64], lkst[r][c], ehi);
             }
             float rlo[4], rhi[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-              const float2 r = csr[blk * 4 + i];
-              rlo[i] = elo[i] * r.x - ehi[i] * r.y;
-              rhi[i] = ehi[i] * r.x + elo[i] * r.y;
+              rlo[i] = elo[i] * cc[b2][i] - ehi[i] * ss[b2][i];
+              rhi[i] = ehi[i] * cc[b2][i] + elo[i] * ss[b2][i];
             }
-            const int klo = blk >> 1, khi = (blk + C::NB) >> 1, w0 = (blk & 1) * 2;
-            ek[klo][w0] = pack_bf16(rlo[0], rlo[1]);
-            ek[klo][w0 + 1] = pack_bf16(rlo[2], rlo[3]);
-            ek[khi][w0] = pack_bf16(rhi[0], rhi[1]);
-            ek[khi][w0 + 1] = pack_bf16(rhi[2], rhi[3]);
+            elc[2 * b2] = pack_bf16(rlo[0], rlo[1]);
+            elc[2 * b2 + 1] = pack_bf16(rlo[2], rlo[3]);
+            ehc[2 * b2] = pack_bf16(rhi[0], rhi[1]);
+            ehc[2 * b2 + 1] = pack_bf16(rhi[2], rhi[3]);
           }
-#pragma unroll
-          for (int kk = 0; kk < C::NCH; ++kk) sc = mfma16x16x32(as_bf16x8(ek[kk]), qf[kk], sc);
+          sr[r] = mfma16x16x32(as_bf16x8(elc), qf[hb], sr[r]);
+          sr[r] = mfma16x16x32(as_bf16x8(ehc), qf[hb + C::NB / 2], sr[r]);
         }
-        // ---- online softmax: lane l%16 is a head, 4 tokens per lane ---------
-        float s2[4];
-        float mx = -INFINITY;
-        const int64_t left = t_end - ts;  // visible tokens from ts on
-        const int n_vis = left < 0 ? 0 : (left < 16 ? (int)left : 16);
+      }
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          s2[i] = (q * 4 + i < n_vis) ? sc[i] * a.scale_log2 : -INFINITY;
-          mx = fmaxf(mx, s2[i]);
-        }
-        mx = max_xor32(max_xor16(mx));
-        if (__ballot(mx > m_run + kRescaleLog2)) {  // lazy rescale, as above
-          const float mn = fmaxf(m_run, mx);
-          const float alpha = fast_exp2(m_run - (mn == -INFINITY ? 0.f : mn));
+      for (int r = 0; r < RPB; ++r)
 #pragma unroll
-          for (int blk = 0; blk < C::NBLK; ++blk) acc[blk] *= alpha;
+        for (int i = 0; i < 4; ++i) sc[i] = slot == r ? sr[r][i] : sc[i];
+    }
+    load_lk(tn);
+    __builtin_amdgcn_sched_barrier(0);
+    base_angles(tn, buf ^ 1);
+    // ---- online softmax: one column per lane, 4 tokens -----------------------
+    float s2[4];
+    float mx = -INFINITY;
+    const int n_vis = max(0, min(t_end_l - ts, SB));  // visible tokens of the sub-block
 #pragma unroll
-          for (int rc = 0; rc < C::RC; ++rc) accl[rc] *= alpha;
-          l_part *= alpha;
-          m_run = mn;
-        }
-        const float ms = (m_run == -INFINITY) ? 0.f : m_run;
-        float p[4];
+    for (int i = 0; i < 4; ++i) {
+      s2[i] = (q * 4 + i < n_vis) ? sc[i] * a.scale_log2 : -INFINITY;
+      mx = fmaxf(mx, s2[i]);
+    }
+    mx = max_xor32(max_xor16(mx));
+    if (__ballot(mx > m_run + kRescaleLog2)) {  // lazy rescale, as above
+      const float mn = fmaxf(m_run, mx);
+      const float alpha = fast_exp2(m_run - (mn == -INFINITY ? 0.f : mn));
 #pragma unroll
-        for (int i = 0; i < 4; ++i) p[i] = fast_exp2(s2[i] - ms);
-        l_part += (p[0] + p[1]) + (p[2] + p[3]);
-        u32x2 pw;
-        pw[0] = pack_bf16(p[0], p[1]);
-        pw[1] = pack_bf16(p[2], p[3]);
-        const i16x4 pb = as_i16x4(pw);
+      for (int blk = 0; blk < C::NBLK; ++blk) acc[blk] *= alpha;
+#pragma unroll
+      for (int rc = 0; rc < C::RC; ++rc) accl[rc] *= alpha;
+      l_part *= alpha;
+      m_run = mn;
+    }
+    const float ms = (m_run == -INFINITY) ? 0.f : m_run;
+    float p[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) p[i] = fast_exp2(s2[i] - ms);
+    l_part += (p[0] + p[1]) + (p[2] + p[3]);
+    const u32x2 pw = {pack_bf16(p[0], p[1]), pack_bf16(p[2], p[3])};
+    const i16x4 pb = as_i16x4(pw);
+    __builtin_amdgcn_wave_barrier();
+    // ---- O^T += V^T P^T; (P L_v)^T += L_v^T P^T, each request its columns ------
+#pragma unroll
+    for (int blk = 0; blk < C::NBLK; ++blk)
+      acc[blk] = mfma16x16x16(lds_read_tr(vl + tr_row * C::V_ROW + blk * 16 + tr_col), pb, acc[blk]);
+    if (has_lv) {
+#pragma unroll
+      for (int r = 0; r < RPB; ++r) {
+        if constexpr (NLT == 1) lv_store(r);
         __builtin_amdgcn_wave_barrier();
-        // ---- O^T += V^T P^T, (P L_v)^T += L_v^T P^T -----------------------
+        const i16x4 pr = as_i16x4(slot == r ? pw : u32x2{0u, 0u});
 #pragma unroll
-        for (int blk = 0; blk < C::NBLK; ++blk)
-          acc[blk] = mfma16x16x16(lds_read_tr(vt + (sb * SB + tr_row) * C::V_ROW + blk * 16 + tr_col), pb, acc[blk]);
-        if (has_lv) {
-#pragma unroll
-          for (int rc = 0; rc < C::RC; ++rc)
-            accl[rc] = mfma16x16x16(lds_read_tr(lvl + tr_row * C::LV_ROW + rc * 16 + tr_col), pb, accl[rc]);
-        }
+        for (int rc = 0; rc < C::RC; ++rc)
+          accl[rc] = mfma16x16x16(lds_read_tr(lvl + (r % NLT) * LVT + tr_row * C::LV_ROW + rc * 16 + tr_col), pr, accl[rc]);
         __builtin_amdgcn_wave_barrier();
+      }
+    }
+    if constexpr (NLT == 1) {
+      load_lv(tn);
+      __builtin_amdgcn_sched_barrier(0);
     }
   }
 
-  if (!active) return;
+  // ---- combine the streams of each group, one partial per (request, head) ----
   l_part += shfl_xor(l_part, 16);
   l_part += shfl_xor(l_part, 32);
-  if (c16 >= G) return;
-  const int64_t hstride = (int64_t)a.n_splits * C::PS;
-  float* wsb = a.ws + ((int64_t)b * a.n_q + (int64_t)g * G + c16) * hstride + (int64_t)split * C::PS;
-  if (q == 0) {
-    wsb[0] = m_run;
-    wsb[1] = l_part;
-  }
+  __syncthreads();  // every wave is done with the loop's LDS
+  float* part = reinterpret_cast<float*>(smem);
+  {
+    float* pr = part + (w * 16 + c16) * PR;
 #pragma unroll
-  for (int blk = 0; blk < C::NBLK; ++blk)
-    *reinterpret_cast<f32x4*>(wsb + 4 + blk * 16 + q * 4) = acc[blk];
-  if (has_lv) {
+    for (int blk = 0; blk < C::NBLK; ++blk) *reinterpret_cast<f32x4*>(pr + blk * 16 + q * 4) = acc[blk];
 #pragma unroll
     for (int rc = 0; rc < C::RC; ++rc)
-      if (rc * 16 + q * 4 < R) *reinterpret_cast<f32x4*>(wsb + 4 + D + rc * 16 + q * 4) = accl[rc];
+      if (rc * 16 + q * 4 < R) *reinterpret_cast<f32x4*>(pr + D + rc * 16 + q * 4) = accl[rc];
+    if (q == 0) {
+      pr[D + R] = m_run;
+      pr[D + R + 1] = l_part;
+    }
   }
+  __syncthreads();
+  constexpr int NV = (D + R) / 4;  // float4 columns of a partial's accumulators
+  const int n_col = RPB * G;
+  auto combine = [&](auto n) {  // compile-time stream count: all reads of an item in flight at once
+    constexpr int NS = decltype(n)::value;
+    for (int e = tid; e < n_grp * n_col * NV; e += NTH) {
+      const int v = e % NV, col = (e / NV) % n_col, gi = e / (NV * n_col);
+      const int rs = col / G, bb = b_wg + gi * RPB + rs;
+      if (bb >= a.batch || (v >= D / 4 && !has_lv)) continue;
+      const float* p0 = part + (gi * NS * 16 + col) * PR;
+      f32x4 x[NS];
+      f32x2 ml[NS];
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {
+        x[s] = *reinterpret_cast<const f32x4*>(p0 + s * 16 * PR + 4 * v);
+        ml[s] = *reinterpret_cast<const f32x2*>(p0 + s * 16 * PR + D + R);
+      }
+      float M = ml[0][0];
+#pragma unroll
+      for (int s = 1; s < NS; ++s) M = fmaxf(M, ml[s][0]);
+      const float Ms = M == -INFINITY ? 0.f : M;
+      f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+      float L = 0.f;
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {
+        const float wt = fast_exp2(ml[s][0] - Ms);
+        L += wt * ml[s][1];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sum[i] += wt * x[s][i];
+      }
+      float* wsb = a.ws + (((int64_t)bb * a.n_q + (int64_t)g * G + (col - rs * G)) * a.n_splits + split) * C::PS;
+      *reinterpret_cast<f32x4*>(wsb + 4 + 4 * v) = sum;
+      if (v == 0) {
+        wsb[0] = M;
+        wsb[1] = L;
+      }
+    }
+  };
+  if (n_grp == 1) combine(std::integral_constant<int, SH_W>{});
+  else combine(std::integral_constant<int, SH_W / 2>{});
 }
 
 // The same merge for rows with at most 16 splits (split prefill, longer
@@ -1080,15 +1186,26 @@ hipError_t launch_t(AttnArgs a, hipStream_t st) {
   return launch_merge_t<D, R>(a, st);
 }
 
-template <int D, int R>
-hipError_t launch_shared_t(AttnArgs a, hipStream_t st) {
-  using C = Dec<D, R>;
-  a.dec_group = C::NW;
-  const int rg = (a.batch + C::NW - 1) / C::NW;
-  hipLaunchKernelGGL((lrsa_decode_shared_kernel<D, R>), dim3(a.n_splits, a.n_kv, rg), dim3(C::NT), 0, st, a);
+template <int D, int R, int RPB>
+hipError_t launch_shared_rpb(AttnArgs a, hipStream_t st) {
+  // One group of requests needs all eight waves as streams; more go two to a
+  // workgroup where their B_k fits.
+  const int n_grp = a.batch > RPB ? sh_groups(R) : 1;
+  a.dec_group = n_grp * RPB;
+  const dim3 grid(a.n_splits, a.n_kv, (a.batch + a.dec_group - 1) / a.dec_group);
+  hipLaunchKernelGGL((lrsa_decode_shared_kernel<D, R, RPB>), grid, dim3(SH_W * 64), 0, st, a, n_grp);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   return launch_merge_t<D, R>(a, st);
+}
+
+template <int D, int R>
+hipError_t launch_shared_t(const AttnArgs& a, hipStream_t st) {
+  switch (sh_rpb(a.group)) {
+    case 4: return launch_shared_rpb<D, R, 4>(a, st);
+    case 3: return launch_shared_rpb<D, R, 3>(a, st);
+    default: return launch_shared_rpb<D, R, 2>(a, st);
+  }
 }
 
 template <int D>
@@ -1119,14 +1236,15 @@ int decode_tile_tokens() { return TK; }
 
 bool decode_shares_base(int batch, int64_t kv_req_stride) { return batch > 1 && kv_req_stride == 0; }
 
-void decode_plan(int64_t s_cap, int batch, int n_kv, int head_dim, int rank, bool shared_base, bool paged, int cus,
-                 int* n_splits) {
+void decode_plan(int64_t s_cap, int batch, int n_kv, int group, int head_dim, int rank, bool shared_base, bool paged,
+                 int cus, int* n_splits) {
   const int64_t tiles = (s_cap + TK - 1) / TK;
-  const int nw = dec_waves(rank);
+  const int nw = shared_base ? SH_W : dec_waves(rank);
   const int64_t nb = batch > 0 ? batch : 1;
   // Workgroups per split: (request, group of nw KV heads) for the per-request
-  // kernel, (KV head, group of nw requests) when the base cache is shared.
-  const int64_t groups = shared_base ? (int64_t)n_kv * ((nb + nw - 1) / nw) : nb * ((n_kv + nw - 1) / nw);
+  // kernel, (KV head, groups of requests) when the base cache is shared.
+  const int64_t rq = sh_rpb(group) * (nb > sh_rpb(group) ? sh_groups(rank) : 1);
+  const int64_t groups = shared_base ? (int64_t)n_kv * ((nb + rq - 1) / rq) : nb * ((n_kv + nw - 1) / nw);
   // Splits for a target of `rounds` 8-wave workgroups per CU.
   auto plan = [&](int64_t rounds, int64_t* ns_out, int64_t* st_out) {
     const int64_t target_wgs = rounds * (cus > 0 ? cus : 1) * 8 / nw;
@@ -1148,9 +1266,11 @@ void decode_plan(int64_t s_cap, int batch, int n_kv, int head_dim, int rank, boo
   // workgroup's whole register file per CU and keeps one sub-block in flight
   // per wave: one round of longer splits measured faster there (64k, 8
   // requests: 426 -> 419 us; two, three and four rounds 426, 442, 446 us).
+  // The shared-base kernel takes one round too: its workgroups' start and
+  // combine cost as much as many sub-blocks (see its comment).
   int64_t ns, st;
   plan(2, &ns, &st);
-  if (st < 8 || (!shared_base && dec_vdma(head_dim, rank, paged))) plan(1, &ns, &st);
+  if (st < 8 || shared_base || dec_vdma(head_dim, rank, paged)) plan(1, &ns, &st);
   *n_splits = (int)ns;
 }
 
