@@ -323,6 +323,7 @@ PRC_API prc_status precompute_lr_cache(const uint16_t* X, int64_t T, int64_t d_i
   a.rank = rank;
   int cus = 0;
   if (prc_status ds = device_ready(&cus)) return ds;
+  a.cus = cus;
   return launch_status(prc::launch_precompute(a, static_cast<hipStream_t>(stream)), "precompute_lr_cache");
 }
 
@@ -399,6 +400,7 @@ prc_status project_impl(const char* who, const uint16_t* X, int64_t T, int64_t d
       a.w2pi[j] = std::pow(rope_theta, -2.0 * j / (double)head_dim) / (2.0 * M_PI);
   int cus = 0;
   if (prc_status ds = device_ready(&cus)) return ds;
+  a.cus = cus;
   return launch_status(prc::launch_precompute(a, stream), who);
 }
 

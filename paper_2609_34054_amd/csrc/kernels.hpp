@@ -121,6 +121,7 @@ struct PrecomputeArgs {
   int64_t tok_offset;
   int32_t n_cols;
   int32_t rank;
+  int32_t cus;          // compute units of the device
   int32_t nkv;          // n_kv * head_dim, a multiple of 64 (or 0)
   int32_t head_dim;
   // Paged output (tbl != nullptr): token p = tok_offset + t is written to row

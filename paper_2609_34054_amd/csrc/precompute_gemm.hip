@@ -100,6 +100,15 @@ __device__ __forceinline__ int key_wcol(int vc, int head_dim) {
   return hd * head_dim + (e / 32) * 16 + (e % 16) + ((e % 32) / 16) * (head_dim / 2);
 }
 
+// Row of the caches (or pools) that holds absolute position trow.
+__device__ __forceinline__ int64_t cache_row(const PrecomputeArgs& a, int64_t trow) {
+  if (a.tbl == nullptr) return trow;
+  const int qb = (int)(trow / a.blk);
+  int32_t e = a.tbl[qb];
+  e = e < 0 ? 0 : (e >= a.nblk ? a.nblk - 1 : e);
+  return (int64_t)e * a.blk + (trow - (int64_t)qb * a.blk);
+}
+
 // Writes one 32 x 32 block of C^T in the 32x32x16 result layout: r[j] is
 // output column cb + (j / 4) * 8 + h * 4 + j % 4 of token t (h = lane / 32).
 // Keys are rotated at the token's position as they are written; every token
@@ -108,13 +117,7 @@ __device__ __forceinline__ void store_block(const PrecomputeArgs& a, const f32x1
                                             int h) {
   if (t >= a.T) return;
   const int64_t trow = a.tok_offset + t;  // absolute position of the token
-  int64_t row = trow;
-  if (a.tbl != nullptr) {
-    const int q = (int)(trow / a.blk);
-    int32_t e = a.tbl[q];
-    e = e < 0 ? 0 : (e >= a.nblk ? a.nblk - 1 : e);
-    row = (int64_t)e * a.blk + (trow - (int64_t)q * a.blk);
-  }
+  const int64_t row = cache_row(a, trow);
   if (region == 0) {
     // Keys: registers j and j + 8 hold dims j0 + i and j0 + i + d/2 of one
     // head (the column order of key tiles); rotate-half RoPE at position trow.
@@ -170,12 +173,15 @@ __global__ void __launch_bounds__((NCW + NPW) * 64) precompute_kernel(const Prec
   const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const bool producer = wv >= NCW;
   const int w = producer ? wv - NCW : wv;
-  // XCD-aware tile order: workgroup L runs on XCD L % 8; consecutive slots of
-  // one XCD walk the column tiles of one token tile.
-  const int L = blockIdx.x, xcd = L % NXCD, slot = L / NXCD;
-  const int ct = slot % n_ct;
-  const int tt = (slot / n_ct) * NXCD + xcd;
-  if (tt >= n_tt) return;  // padding of the grid (uniform over the workgroup)
+  // XCD-aware tile order: workgroup L runs on XCD L % 8, and each XCD takes a
+  // contiguous eighth of the tiles, column tiles fastest: the column tiles
+  // that share rows of X run on one XCD, and few token tiles still spread
+  // over all of them (16 tokens x 2304 columns: 31.6 us with all column tiles
+  // of a token tile on one XCD, 19.1 us so; 4096 tokens: 109 -> 102 us).
+  const int n_tiles = n_ct * n_tt, per = (n_tiles + NXCD - 1) / NXCD;
+  const int tile = (int)(blockIdx.x % NXCD) * per + (int)(blockIdx.x / NXCD);
+  if ((int)(blockIdx.x / NXCD) >= per || tile >= n_tiles) return;  // padding of the grid (uniform over the workgroup)
+  const int ct = tile % n_ct, tt = tile / n_ct;
   const int col0 = ct * TB;
   const int64_t tok0 = (int64_t)tt * TB;
   // Column regions (tiles never straddle them: nkv is a multiple of TB):
@@ -345,10 +351,95 @@ template <int TB>
 hipError_t launch_tb(const PrecomputeArgs& a, hipStream_t st) {
   const int n_ct = 2 * a.nkv / TB + (a.n_cols + TB - 1) / TB;
   const int n_tt = (int)((a.T + TB - 1) / TB);
-  const int groups = (n_tt + NXCD - 1) / NXCD;  // token tiles per XCD
-  const int grid = groups * NXCD * n_ct;
+  const int grid = (n_ct * n_tt + NXCD - 1) / NXCD * NXCD;
   hipLaunchKernelGGL((precompute_kernel<TB>), dim3(grid), dim3((NCW + NPW) * 64), 0, st, a, n_ct, n_tt);
   return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------
+// LR precompute of few rows or few columns: not enough 64 x 64 tiles to occupy
+// the chip (512 rows x 128 columns make 16).  A CU streams its operands at a
+// fixed rate, so what counts is the bytes of one workgroup's tile: 16 tokens x
+// 32 columns here, 48 rows of k against 128, over eight times the workgroups.
+// The eight waves each take a slice of k and are summed through LDS in a fixed
+// order.  Nothing is staged in LDS: a lane loads 16 bytes of a token row of X
+// (the MFMA B operand as it is) and two columns of eight weight rows, which it
+// transposes in registers (v_perm_b32) into two A fragments: fragment j holds
+// columns 2 c + j, c = lane % 16.
+// Measured, d_in 4096, against 64 x 64 tiles: 512 x 128 17.6 -> 12.3 us, 64 x
+// 256 17.3 -> 9.8 us, 1000 x 128 17.6 -> 13.0 us, 512 x 256 (one workgroup per
+// CU) 17.8 -> 13.8 us; 1500 x 256 (three per CU) 18.0 -> 30.9 us.  Larger tiles
+// of this form (32 x 32, 16 x 64, 32 x 64) and deeper rings measured slower.
+constexpr int SM_W = 8;   // waves per workgroup (k slices)
+constexpr int SM_U = 4;   // 32-k steps in flight per wave
+constexpr int SM_TC = 32, SM_TT = 16;  // columns and tokens per workgroup
+
+__global__ void __launch_bounds__(SM_W * 64) precompute_small_kernel(const PrecomputeArgs a) {
+  __shared__ float part[SM_W][8][64];
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int q = lane >> 4, c16 = lane & 15;
+  const int c0 = blockIdx.x * SM_TC;
+  const int64_t tok0 = (int64_t)blockIdx.y * SM_TT;
+  const int toks = (int)(a.T - tok0 < SM_TT ? a.T - tok0 : (int64_t)SM_TT);
+  const int32_t ldw2 = a.n_cols * 2, ldx2 = (int32_t)(a.ld_x * 2), d_in = (int32_t)a.d_in;
+  const auto rw = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(a.A), (short)0, d_in * ldw2, 0x00020000);
+  const auto rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(a.X + tok0 * a.ld_x), (short)0,
+                                                    (toks - 1) * ldx2 + d_in * 2, 0x00020000);
+  const int nk = (d_in + 31) / 32;  // 32-k steps; this wave's slice of them
+  const int s_lo = nk * w / SM_W, s_hi = nk * (w + 1) / SM_W;
+  // Per-lane byte offsets; a step adds uniform strides.  Columns past n_cols,
+  // chunks of X past d_in and steps past the slice are pointed out of range,
+  // weight rows past d_in fall outside their resource: all read as zeros.
+  const bool col_ok = c0 + 2 * c16 < a.n_cols;  // n_cols is a multiple of 8
+  const int32_t woff = 8 * q * ldw2 + (c0 + 2 * c16) * 2, xoff = c16 * ldx2 + 16 * q;
+  struct Step {
+    uint32_t w[8];  // two columns of rows 32 s + 8 q + i
+    u32x4 x;        // X of token c16, k = 32 s + 8 q ..
+  };
+  auto load = [&](Step& st, int s) {
+    const int32_t wo = s < s_hi && col_ok ? woff + s * 32 * ldw2 : INT32_MIN;
+    const int32_t xo = s < s_hi && 32 * s + 8 * q < d_in ? xoff + 64 * s : INT32_MIN;  // d_in is a multiple of 8
+#pragma unroll
+    for (int i = 0; i < 8; ++i) st.w[i] = __builtin_amdgcn_raw_buffer_load_b32(rw, wo + i * ldw2, 0, 0);
+    st.x = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rx, xo, 0, 0));
+  };
+  f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+  Step ring[SM_U];
+#pragma unroll
+  for (int u = 0; u < SM_U; ++u) load(ring[u], s_lo + u);
+  for (int s = s_lo; s < s_hi; s += SM_U) {
+#pragma unroll
+    for (int u = 0; u < SM_U; ++u) {
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        u32x4 f;
+#pragma unroll
+        for (int p = 0; p < 4; ++p)
+          f[p] = __builtin_amdgcn_perm(ring[u].w[2 * p + 1], ring[u].w[2 * p], j ? 0x07060302u : 0x05040100u);
+        acc[j] = mfma16x16x32(as_bf16x8(f), as_bf16x8(ring[u].x), acc[j]);
+      }
+      load(ring[u], s + SM_U + u);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) part[w][4 * j + i][lane] = acc[j][i];
+  __syncthreads();
+  // Columns 2 c, 2 c + 1 of token t, one thread each: lane 16 (c / 4) + t of
+  // rows c % 4 and 4 + c % 4.
+  if (tid >= SM_TT * SM_TC / 2) return;
+  const int t = tid / (SM_TC / 2), c = tid % (SM_TC / 2), col = c0 + 2 * c;
+  if (t >= toks || col >= a.n_cols) return;
+  float v[2] = {0.f, 0.f};
+#pragma unroll
+  for (int ww = 0; ww < SM_W; ++ww)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) v[j] += part[ww][4 * j + c % 4][16 * (c / 4) + t];
+  const int64_t plane = col / a.rank, jr = col - plane * a.rank;
+  *reinterpret_cast<uint32_t*>(a.L + (plane * a.s_cap + cache_row(a, a.tok_offset + tok0 + t)) * a.rank + jr) =
+      pack_bf16(v[0], v[1]);
 }
 
 // A handful of rows (the K/V and LR rows of newly decoded tokens) is a
@@ -483,11 +574,12 @@ __global__ void __launch_bounds__(64 * GV_W) project_gemv_kernel(const Precomput
     x += red[i][0][t][e];
     y += red[i][1][t][e];
   }
-  const int64_t row = a.tok_offset + t;  // absolute position and cache row
+  const int64_t pos = a.tok_offset + t;  // absolute position
+  const int64_t row = cache_row(a, pos);
   if (region == 0) {
     const int hd = c0 / a.head_dim, j = c0 - hd * a.head_dim + e;
     float cs, sn;
-    rope_cs((int)row, a.w2pi[j], cs, sn);
+    rope_cs((int)pos, a.w2pi[j], cs, sn);
     uint16_t* kp = a.Kout + row * a.nkv + hd * a.head_dim + j;
     kp[0] = (uint16_t)(pack_bf16(x * cs - y * sn, 0.f) & 0xffffu);
     kp[half] = (uint16_t)(pack_bf16(y * cs + x * sn, 0.f) & 0xffffu);
@@ -503,16 +595,28 @@ __global__ void __launch_bounds__(64 * GV_W) project_gemv_kernel(const Precomput
 }  // namespace
 
 hipError_t launch_precompute(const PrecomputeArgs& a, hipStream_t st) {
-  if (a.tbl == nullptr && a.T <= GV_T) {
+  const int64_t cus = a.cus;
+  if (a.T <= GV_T) {
     const int units = a.nkv / 16 + a.nkv / 8 + a.n_cols / 8;
     hipLaunchKernelGGL(project_gemv_kernel, dim3(64 * ((units + 63) / 64)), dim3(64 * GV_W), 0, st, a, units);
     return hipGetLastError();
   }
-  // 128-wide tiles halve the bytes loaded per MFMA but need enough of them to
-  // fill the CUs; the K/V boundary must fall on a tile edge.
-  const int64_t wide = (int64_t)((2 * a.nkv + a.n_cols + 127) / 128) * ((a.T + 127) / 128);
-  if (a.nkv % 128 == 0 && wide >= 256) return launch_tb<128>(a, st);
-  return launch_tb<64>(a, st);
+  const auto cdiv = [](int64_t x, int64_t y) { return (x + y - 1) / y; };
+  // LR rows alone: small tiles while they make at most one workgroup per CU
+  // (beyond that they move more bytes per CU than 64 x 64 tiles do).
+  const int64_t sm_x = cdiv(a.n_cols, SM_TC), sm_y = cdiv(a.T, SM_TT);
+  if (a.nkv == 0 && sm_x * sm_y <= cus) {
+    hipLaunchKernelGGL(precompute_small_kernel, dim3((unsigned)sm_x, (unsigned)sm_y), dim3(SM_W * 64), 0, st, a);
+    return hipGetLastError();
+  }
+  // A CU takes one workgroup at a time and streams the tile's operands at a
+  // fixed rate, so a launch takes its rounds of the CUs times the time of one
+  // tile: at d_in 4096, 17-19 us for 64 x 64 and 32-36 us for 128 x 128
+  // (measured from 1 to 600 tiles).  The K/V boundary must fall on a tile edge.
+  const int64_t n64 = (2 * a.nkv / 64 + cdiv(a.n_cols, 64)) * cdiv(a.T, 64);
+  const int64_t n128 = (2 * a.nkv / 128 + cdiv(a.n_cols, 128)) * cdiv(a.T, 128);
+  const double t64 = 18.5 * (double)cdiv(n64, cus), t128 = a.nkv % 128 == 0 ? 36.0 * (double)cdiv(n128, cus) : 1e30;
+  return t128 < t64 ? launch_tb<128>(a, st) : launch_tb<64>(a, st);
 }
 
 }  // namespace prc

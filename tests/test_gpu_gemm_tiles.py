@@ -1,0 +1,81 @@
+"""The projection and precompute GEMMs at the edges of their tile choices: tails
+of k (d_in below one step, below one step per wave, not a multiple of 32),
+partial token and column tiles, contiguous and paged rows, against the fp64
+oracle.  Tolerances: relative 2-norm 1e-2 as everywhere; each element within
+2^-7 of its size (bf16 rounding is 2^-9) plus 2e-2 of unit-scale outputs."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2609_34054_amd as prc
+from gpu_cases import PRE_REL, f64
+from test_gpu_paged import block_table
+from workload.gen import normal_bf16
+
+pytestmark = pytest.mark.gpu
+
+# id, T, d_in, n_kv, d, n_proj, N, r, tok_offset, block size (0: contiguous)
+CASES = [
+    # LR rows alone, small tiles (16 tokens x 32 columns, k over eight waves).
+    ("small_one_chunk", 5, 8, 0, 64, 1, 1, 8, 0, 0),
+    ("small_k_tail", 17, 264, 0, 64, 2, 3, 8, 7, 0),
+    ("small_k_24", 16, 24, 0, 64, 1, 5, 8, 1, 0),
+    ("small_paged", 33, 520, 0, 64, 2, 2, 16, 60, 64),
+    ("small_most_tiles", 512, 320, 0, 64, 2, 4, 32, 3, 0),
+    ("one_tile_too_many", 513, 96, 0, 64, 2, 4, 32, 3, 0),
+    # Matrix-vector rows into paged caches.
+    ("gemv_paged", 3, 264, 2, 64, 2, 2, 16, 126, 128),
+    ("gemv_paged_lr", 1, 512, 0, 64, 2, 3, 64, 64, 64),
+    # 64- and 128-wide tiles: few token tiles over all XCDs, odd tile counts.
+    ("tiles_one_token_tile", 6, 72, 8, 128, 2, 3, 8, 250, 0),
+    ("tiles_three_paged", 150, 136, 4, 128, 2, 3, 16, 50, 128),
+    ("tiles_128_ragged", 500, 264, 8, 128, 2, 8, 16, 5, 0),
+    ("tiles_d64", 700, 104, 6, 64, 1, 3, 64, 0, 64),
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
+def test_gemm_edges(case):
+    cid, T, d_in, n_kv, d, n_proj, N, r, off, blk = case
+    print(f"gemm {cid}", flush=True)
+    theta, g, sentinel = 5e5, 7000 + 10 * len(cid), -7.0
+    X = normal_bf16((T, d_in), 1.0, g + 1)
+    W = normal_bf16((d_in, 2 * n_kv * d), 1.0 / math.sqrt(d_in), g + 2)
+    A = normal_bf16((d_in, n_proj * N * r), 1.0 / math.sqrt(d_in), g + 3)
+    rows = np.arange(off, off + T)
+    full = lambda *shape: torch.full(shape, sentinel, dtype=torch.bfloat16, device="cuda")  # noqa: E731
+    if blk:
+        mb = -(-(off + T) // blk)
+        tbl = block_table(1, mb, mb + 2, 5)[0]
+        L = full(n_proj, N, mb + 2, blk, r)
+        K = full(mb + 2, blk, n_kv, d) if n_kv else None
+        V = full(mb + 2, blk, n_kv, d) if n_kv else None
+        prc.project_kv_and_lr_cache_paged(X.cuda(), W.cuda() if n_kv else None, A.cuda(), n_kv, d, n_proj, N, r, K, V,
+                                          L, tbl.cuda(), rope_theta=theta, tok_offset=off)
+        at = tbl.numpy()[rows // blk].astype(np.int64) * blk + rows % blk
+    else:
+        s_cap = off + T + 3
+        L = full(n_proj, N, s_cap, r)
+        K, V = (full(s_cap, n_kv, d), full(s_cap, n_kv, d)) if n_kv else (None, None)
+        if n_kv:
+            prc.project_kv_and_lr_cache(X.cuda(), W.cuda(), A.cuda(), n_kv, d, n_proj, N, r, K, V, L,
+                                        rope_theta=theta, tok_offset=off)
+        else:
+            prc.precompute_lr_cache(X.cuda(), A.cuda(), n_proj, N, r, L, tok_offset=off)
+        at = rows
+    torch.cuda.synchronize()
+    outs = [("L", f64(L).reshape(n_proj, N, -1, r), oracle.precompute_lr_cache(f64(X), f64(A), n_proj, N, r), 2)]
+    if n_kv:
+        Wn = f64(W)
+        Kr, Vr, _ = oracle.project_kv_and_lr(f64(X), Wn[:, :n_kv * d], Wn[:, n_kv * d:], f64(A), n_kv, n_proj, N, r,
+                                             rows, theta)
+        outs += [("K", f64(K).reshape(-1, n_kv, d), Kr, 0), ("V", f64(V).reshape(-1, n_kv, d), Vr, 0)]
+    for name, got, ref, axis in outs:
+        mine = np.take(got, at, axis=axis)
+        assert np.linalg.norm(mine - ref) / np.linalg.norm(ref) <= PRE_REL, name
+        assert np.max(np.abs(mine - ref) - 2 ** -7 * np.abs(ref)) <= 2e-2, name
+        rest = np.delete(got, at, axis=axis)
+        assert (rest == sentinel).all(), name  # rows outside the segment are untouched
