@@ -27,7 +27,10 @@
 // swizzle is applied by choosing which global chunk each lane fetches.
 // Tokens past T, k past d_in and LR columns past n_cols read as zeros.  The
 // result layout gives each lane 4 consecutive output columns of one token: one
-// 8-byte store.  Block order is XCD-aware: the column tiles that share rows of
+// 8-byte store.  Calls of 1 to 4 rows, LR precompute too narrow to fill the chip
+// with such tiles, and wide problems have kernels of their own below; the
+// launch picks by a model of the rounds each takes.
+// Block order is XCD-aware: the column tiles that share rows of
 // X run on the same XCD, so X is fetched into each L2 once.
 #include "common.hpp"
 #include "kernels.hpp"
@@ -357,6 +360,286 @@ hipError_t launch_tb(const PrecomputeArgs& a, hipStream_t st) {
 }
 
 // ---------------------------------------------------------------------------
+// Wide problems (the joined projection of a long segment).  A CU streams its
+// tile's operands at a fixed rate (about 30 bytes a clock here), so a 128 x 128
+// tile is bound by its 256 rows of loads, and 576 such tiles (4096 x 2304) are
+// 2.25 rounds of the CUs besides.  This kernel takes 256 tokens x 16 NB columns
+// per workgroup: 1.5 times the flops per byte, and the launch picks NB so that
+// the tiles come out near a whole number of rounds.
+// Four compute waves (2 x 2, each 128 tokens x 8 NB columns on 16x16x32 MFMAs)
+// and four loader waves filling a three-stage LDS ring of 64 k with direct
+// global->LDS loads.  X rows are XOR-swizzled in 16-byte chunks; weight rows
+// lie as in memory, in 16-column units, rotated by row so that the eight rows
+// a transposing read serves together (two groups of four, 8 rows apart) hit
+// different banks.  A unit holds 16 value or LR columns, or 8 key dims and
+// their 8 RoPE partners (which land in lanes l and l ^ 32 of the result).
+// 4096 x 2304, d_in 4096: 107 us with 128 x 128 tiles, 71 us (1.09 PFLOP/s)
+// with 256 x 160; alone on its CU a 256 x 160 tile takes 56 us, 33 of them
+// MFMAs at their full rate and about 10 before the first stage and after the
+// last.  Measured and slower: fragments read at the head of each stage instead
+// of between the MFMAs of the step before (77 us); the compute waves issuing
+// the weight loads (80 us: a full load queue stalls their MFMAs too).
+constexpr int WD_TT = 256;  // tokens per workgroup
+constexpr int WD_KS = 64;   // k per stage
+constexpr int WD_NST = 3;   // stages
+constexpr int WD_NL = 4;    // loader waves
+
+template <int NB>
+struct Wide {
+  static constexpr int UW = NB / 2;  // units per compute wave
+  static constexpr int XB = WD_TT * WD_KS * 2, WB = WD_KS * NB * 32, SB = XB + WB;  // bytes per stage
+  static constexpr int NXI = XB / 1024, NWI = WB / 1024, NI = (NXI + NWI) / WD_NL;  // 1 KB loads; per loader wave
+  static_assert(NB % 2 == 0 && (NXI + NWI) % WD_NL == 0 && WB % 1024 == 0, "even shares");
+  // Units by which row r of the weight tile is rotated: the bank of unit u is
+  // (r NB + u) mod 8 groups of 8 banks.
+  static __device__ __forceinline__ int rot(int r) { return NB % 8 == 0 ? (r & 3) + 4 * ((r >> 3) & 1) : (r >> 3) & 1; }
+};
+
+template <int NB>
+__global__ void __launch_bounds__((4 + WD_NL) * 64, 2) project_wide_kernel(const PrecomputeArgs a, int n_wt, int n_ct, int n_tt) {
+  using C = Wide<NB>;
+  __shared__ __attribute__((aligned(1024))) char ring[WD_NST * C::SB];
+  __shared__ double w2pi_lds[kMaxHalfDim];    // the epilogue's RoPE frequencies,
+  __shared__ float2 rot16_lds[kMaxHalfDim];   // and their rotation by 16 positions
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // Each XCD takes a contiguous eighth of the tiles, column tiles fastest.
+  const int n_tiles = n_ct * n_tt, per = (n_tiles + NXCD - 1) / NXCD;
+  const int tile = (int)(blockIdx.x % NXCD) * per + (int)(blockIdx.x / NXCD);
+  if ((int)(blockIdx.x / NXCD) >= per || tile >= n_tiles) return;  // uniform over the workgroup
+  const int ct = tile % n_ct, tt = tile / n_ct;
+  const int64_t tok0 = (int64_t)tt * WD_TT;
+  const int toks = (int)(a.T - tok0 < WD_TT ? a.T - tok0 : (int64_t)WD_TT);
+  // Column tiles 0 .. n_wt - 1 are units of W (n_ku key units, then as many of
+  // values), the others of A.
+  const bool lr = ct >= n_wt;
+  const int half = a.head_dim / 2, n_ku = a.nkv / 16;
+  const int u0 = (lr ? ct - n_wt : ct) * NB, n_un = lr ? (a.n_cols + 15) / 16 : 2 * n_ku;  // first unit; units of the matrix
+  const int d_in = (int)a.d_in, nstage = (d_in + WD_KS - 1) / WD_KS;
+  // First column of 8-column chunk hc of unit U within its weight matrix.
+  auto unit_col = [&](int U, int hc) {
+    if (lr || U >= n_ku) return U * 16 + hc * 8;  // value units follow the key units' nkv columns
+    const int hd = U * 8 / half;
+    return hd * a.head_dim + (U * 8 - hd * half) + hc * half;
+  };
+
+  if (wv >= 4) {
+    // ---- loaders ---------------------------------------------------------------
+    const int w = wv - 4;
+    const int32_t ldw = lr ? a.n_cols * 2 : a.nkv * 4;  // weight row stride (bytes)
+    const i32x4 rx = buffer_rsrc(a.X + tok0 * a.ld_x, (int32_t)((toks - 1) * a.ld_x * 2 + a.d_in * 2));
+    const i32x4 rw = buffer_rsrc(lr ? a.A : a.W, d_in * ldw);
+    // Instruction j of this wave is load j WD_NL + w of the stage: X rows
+    // first, then weight rows.  Offsets at k = 0 (INT32_MIN: columns past the
+    // matrix, read as zeros) and each lane's first k.
+    int32_t off[C::NI], kof[C::NI];
+#pragma unroll
+    for (int j = 0; j < C::NI; ++j) {
+      const int li = j * WD_NL + w;
+      if (j * WD_NL < C::NXI) {
+        const int r = li * 8 + lane / 8, c = (lane % 8) ^ ((r >> 1) & 7);
+        kof[j] = c * 8;
+        off[j] = r * (int32_t)(a.ld_x * 2) + c * 16;
+      } else {
+        const int b = (li - C::NXI) * 1024 + lane * 16, r = b / (NB * 32), pc = (b % (NB * 32)) / 16;
+        const int U = u0 + (pc / 2 + NB - C::rot(r)) % NB, hc = pc % 2;  // the unit stored here
+        const int col = unit_col(U, hc);
+        kof[j] = r;
+        off[j] = U < n_un && (!lr || col < a.n_cols) ? r * ldw + col * 2 : INT32_MIN;
+      }
+    }
+    auto issue = [&](int s) {
+      char* st = ring + (s % WD_NST) * C::SB;
+      const int k0 = s * WD_KS;
+      if (k0 + WD_KS <= d_in) {  // whole stage: the k offset is scalar
+#pragma unroll
+        for (int j = 0; j < C::NI; ++j) {
+          const int li = j * WD_NL + w;
+          if (j * WD_NL < C::NXI) lds_dma16(rx, st + li * 1024, off[j], k0 * 2);
+          else lds_dma16(rw, st + C::XB + (li - C::NXI) * 1024, off[j], k0 * ldw);
+        }
+        return;
+      }
+#pragma unroll
+      for (int j = 0; j < C::NI; ++j) {
+        const int li = j * WD_NL + w;
+        const bool ok = k0 + kof[j] < d_in && off[j] != INT32_MIN;
+        if (j * WD_NL < C::NXI)
+          lds_dma16(rx, st + li * 1024, ok ? off[j] + k0 * 2 : INT32_MIN, 0);
+        else
+          lds_dma16(rw, st + C::XB + (li - C::NXI) * 1024, ok ? off[j] + k0 * ldw : INT32_MIN, 0);
+      }
+    };
+    static_assert(C::NXI % WD_NL == 0 && C::NI < 64, "X and weight loads are separate instructions of every wave");
+    issue(0);
+    if (nstage > 1) issue(1);
+    for (int s = 0; s < nstage; ++s) {
+      // Stage s has landed once only stage s + 1's loads are still in flight.
+      if (s + 1 < nstage) __builtin_amdgcn_s_waitcnt(vmcnt_imm(C::NI));
+      else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+      __syncthreads();  // stage s visible to all; stage s - 1 consumed by all
+      if (s + 2 < nstage) issue(s + 2);  // into the slot of stage s - 1
+    }
+    return;
+  }
+
+  if (!lr && tid < half) {
+    const double wj = a.w2pi[tid];
+    float c, sn;
+    rope_cs(16, wj, c, sn);
+    w2pi_lds[tid] = wj;
+    rot16_lds[tid] = make_float2(c, sn);
+  }
+  // ---- compute waves -------------------------------------------------------------
+  const int q = lane >> 4, c16 = lane & 15, wr = wv >> 1, wc = wv & 1;
+  f32x4 acc[C::UW][8];
+#pragma unroll
+  for (int u = 0; u < C::UW; ++u)
+#pragma unroll
+    for (int m = 0; m < 8; ++m) acc[u][m] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // LDS byte offsets of this lane within a stage: X rows 128 wr + 16 m + c16,
+  // chunk 4 kk + q; weight rows 32 kk + 8 q + c16 / 4 (+ 4), columns
+  // 4 (c16 % 4) .. + 3 of each unit.
+  const int xo = (128 * wr + c16) * (WD_KS * 2), xs = (c16 >> 1) & 7;
+  const int kr = 8 * q + (c16 >> 2), rt = C::rot(kr);  // rows kr + 32 kk and kr + 4 rotate alike
+  int wo[C::UW];
+#pragma unroll
+  for (int u = 0; u < C::UW; ++u)
+    wo[u] = C::XB + kr * (NB * 32) + ((wc * C::UW + u + rt) % NB) * 32 + (c16 & 3) * 8;
+  // Software pipeline over k32 steps: the weight fragments of the next step and
+  // the X fragments four token blocks ahead are read between the MFMAs of this
+  // one (a second full set of X fragments would not fit the registers).  The barrier that publishes
+  // stage s + 1 sits in the middle of the last step of stage s, after its last
+  // read, so that the MFMAs of four token blocks cover the first reads of the
+  // next stage (one compute wave per SIMD: nothing else does).
+  u32x2 fwl[2][C::UW], fwh[2][C::UW];
+  u32x4 fx[4];
+  auto read_w = [&](int set, int u, const char* st, int kk) {
+    const char* p = st + wo[u] + 32 * kk * (NB * 32);
+    fwl[set][u] = lds_read_tr(reinterpret_cast<const uint16_t*>(p));
+    fwh[set][u] = lds_read_tr(reinterpret_cast<const uint16_t*>(p + 4 * (NB * 32)));
+  };
+  auto read_x = [&](int m, const char* st, int kk) {
+    fx[m % 4] = *reinterpret_cast<const u32x4*>(st + xo + m * (16 * WD_KS * 2) + (((4 * kk + q) ^ xs) * 16));
+  };
+  __syncthreads();  // stage 0 visible
+#pragma unroll
+  for (int u = 0; u < C::UW; ++u) read_w(0, u, ring, 0);
+#pragma unroll
+  for (int m = 0; m < 4; ++m) read_x(m, ring, 0);
+  const char* st = ring;
+  int slot = 0;
+  for (int s = 0; s < nstage; ++s) {
+    slot = slot + 1 == WD_NST ? 0 : slot + 1;
+    const char* stn = ring + slot * C::SB;  // stage s + 1 (past the last: stale rows, unused)
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) {
+#pragma unroll
+      for (int m = 0; m < 8; ++m) {
+        if (kk == 1 && m == 4) {
+          __builtin_amdgcn_sched_barrier(0);
+          if (s + 1 < nstage) __syncthreads();  // stage s + 1 visible; stage s consumed
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        const bf16x8 x = as_bf16x8(fx[m % 4]);
+#pragma unroll
+        for (int u = 0; u < C::UW; ++u)
+          acc[u][m] = mfma16x16x32(
+              as_bf16x8(u32x4{fwl[kk][u][0], fwl[kk][u][1], fwh[kk][u][0], fwh[kk][u][1]}), x, acc[u][m]);
+        if (m < 4) read_x(m + 4, st, kk);
+        else read_x(m - 4, kk == 0 ? st : stn, kk ^ 1);
+        // Weight fragments of the next step, spread over this one's blocks
+        // (the second step's only after the barrier).
+#pragma unroll
+        for (int u = 0; u < C::UW; ++u)
+          if (kk == 0 ? u == m : u * 4 / C::UW == m - 4) read_w(kk ^ 1, u, kk == 0 ? st : stn, kk ^ 1);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    st = stn;
+  }
+
+  // acc[u][m][i]: column 4 q + i of unit u0 + wc UW + u, token 128 wr + 16 m + c16.
+  int64_t rowm[8];  // cache row of each token block's token of this lane
+#pragma unroll
+  for (int m = 0; m < 8; ++m) {
+    const int64_t trow = a.tok_offset + tok0 + 128 * wr + 16 * m + c16;
+    rowm[m] = 128 * wr + 16 * m + c16 < toks ? cache_row(a, trow) : 0;
+  }
+#pragma unroll
+  for (int u = 0; u < C::UW; ++u) {
+    const int U = u0 + wc * C::UW + u;
+    if (U >= n_un) break;  // uniform over the wave
+    if (!lr && U < n_ku) {
+      // Keys: lanes q < 2 hold dims j .. j + 3, lanes q + 2 their partners.
+      const int hd = U * 8 / half, j0 = U * 8 - hd * half + 4 * (q & 1);
+      const int pos0 = (int)(a.tok_offset + tok0) + 128 * wr + c16;
+      uint16_t* kp = a.Kout + hd * a.head_dim + j0 + (q >= 2 ? half : 0);
+      double wj[4];
+      float cd[4], sd[4], cs[4], sn[4];  // rotation by 16 positions; angle of token block m
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        wj[i] = w2pi_lds[j0 + i];
+        cd[i] = rot16_lds[j0 + i].x;
+        sd[i] = rot16_lds[j0 + i].y;
+      }
+#pragma unroll
+      for (int m = 0; m < 8; ++m) {
+        float o[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          if (m % 4 == 0) {
+            rope_cs(pos0 + 16 * m, wj[i], cs[i], sn[i]);
+          } else {
+            const float c = cs[i] * cd[i] - sn[i] * sd[i];
+            sn[i] = sn[i] * cd[i] + cs[i] * sd[i];
+            cs[i] = c;
+          }
+          const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc[u][m][i]), __float_as_uint(acc[u][m][i]), false, false);
+          const float x = __uint_as_float(r[0]), y = __uint_as_float(r[1]);  // lanes l % 32 and l % 32 + 32
+          o[i] = q < 2 ? x * cs[i] - y * sn[i] : y * cs[i] + x * sn[i];
+        }
+        if (128 * wr + 16 * m + c16 < toks)
+          *reinterpret_cast<u32x2*>(kp + rowm[m] * a.nkv) = u32x2{pack_bf16(o[0], o[1]), pack_bf16(o[2], o[3])};
+      }
+      continue;
+    }
+    uint16_t* op;
+    int64_t ld;
+    const int c = U * 16 + 4 * q;
+    if (lr) {
+      if (c >= a.n_cols) continue;
+      const int64_t plane = c / a.rank;
+      op = a.L + plane * a.s_cap * a.rank + (c - plane * a.rank);
+      ld = a.rank;
+    } else {
+      op = a.Vout + (c - a.nkv);
+      ld = a.nkv;
+    }
+#pragma unroll
+    for (int m = 0; m < 8; ++m)
+      if (128 * wr + 16 * m + c16 < toks)
+        *reinterpret_cast<u32x2*>(op + rowm[m] * ld) =
+            u32x2{pack_bf16(acc[u][m][0], acc[u][m][1]), pack_bf16(acc[u][m][2], acc[u][m][3])};
+  }
+}
+
+template <int NB>
+int64_t wide_tiles(const PrecomputeArgs& a, int* n_wt, int* n_ct) {
+  *n_wt = (a.nkv / 8 + NB - 1) / NB;
+  *n_ct = *n_wt + ((a.n_cols + 15) / 16 + NB - 1) / NB;
+  return (int64_t)*n_ct * ((a.T + WD_TT - 1) / WD_TT);
+}
+
+template <int NB>
+hipError_t launch_wide(const PrecomputeArgs& a, hipStream_t st) {
+  int n_wt, n_ct;
+  const int64_t tiles = wide_tiles<NB>(a, &n_wt, &n_ct);
+  hipLaunchKernelGGL((project_wide_kernel<NB>), dim3((unsigned)((tiles + NXCD - 1) / NXCD * NXCD)), dim3((4 + WD_NL) * 64), 0,
+                     st, a, n_wt, n_ct, (int)((a.T + WD_TT - 1) / WD_TT));
+  return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------
 // LR precompute of few rows or few columns: not enough 64 x 64 tiles to occupy
 // the chip (512 rows x 128 columns make 16).  A CU streams its operands at a
 // fixed rate, so what counts is the bytes of one workgroup's tile: 16 tokens x
@@ -609,14 +892,35 @@ hipError_t launch_precompute(const PrecomputeArgs& a, hipStream_t st) {
     hipLaunchKernelGGL(precompute_small_kernel, dim3((unsigned)sm_x, (unsigned)sm_y), dim3(SM_W * 64), 0, st, a);
     return hipGetLastError();
   }
-  // A CU takes one workgroup at a time and streams the tile's operands at a
-  // fixed rate, so a launch takes its rounds of the CUs times the time of one
-  // tile: at d_in 4096, 17-19 us for 64 x 64 and 32-36 us for 128 x 128
-  // (measured from 1 to 600 tiles).  The K/V boundary must fall on a tile edge.
-  const int64_t n64 = (2 * a.nkv / 64 + cdiv(a.n_cols, 64)) * cdiv(a.T, 64);
-  const int64_t n128 = (2 * a.nkv / 128 + cdiv(a.n_cols, 128)) * cdiv(a.T, 128);
-  const double t64 = 18.5 * (double)cdiv(n64, cus), t128 = a.nkv % 128 == 0 ? 36.0 * (double)cdiv(n128, cus) : 1e30;
-  return t128 < t64 ? launch_tb<128>(a, st) : launch_tb<64>(a, st);
+  // A CU takes one workgroup at a time, so a launch takes its rounds of the CUs
+  // times the time of one tile: a fixed part and one that goes with d_in
+  // (microseconds, the latter at 4096; measured at 256, 4096 and 5120 from 1 to
+  // 600 tiles).  64 x 64 and 128 x 128 tiles are bound by the CU's load rate,
+  // the 256-token ones by their MFMAs.  Over rounds that are nearly empty the
+  // smaller tile wins (1000 tokens x 2304 columns: 57, 35, 48, 56, 65 us in
+  // this order), over full ones the larger (4096 x 2304: 188, 107, 93, 97, 71
+  // us; 2048 x 2816, d_in 5120: 148, 86, 67, 60, 71 us).  128-wide tiles need
+  // the K/V boundary on a tile edge.
+  int n_wt, n_ct;
+  const double kd = (double)a.d_in / 4096.0;
+  const auto model = [&](double fixed, double per_k, int64_t tiles) { return (fixed + per_k * kd) * (double)cdiv(tiles, cus); };
+  const double t[5] = {
+      model(2.7, 15.8, (2 * a.nkv / 64 + cdiv(a.n_cols, 64)) * cdiv(a.T, 64)),
+      a.nkv % 128 == 0 ? model(5.0, 31.0, (2 * a.nkv / 128 + cdiv(a.n_cols, 128)) * cdiv(a.T, 128)) : 1e30,
+      model(5.0, 45.0, wide_tiles<6>(a, &n_wt, &n_ct)),
+      model(6.6, 42.4, wide_tiles<8>(a, &n_wt, &n_ct)),
+      model(8.4, 49.6, wide_tiles<10>(a, &n_wt, &n_ct)),
+  };
+  int best = 0;
+  for (int i = 1; i < 5; ++i)
+    if (t[i] < t[best]) best = i;
+  switch (best) {
+    case 0: return launch_tb<64>(a, st);
+    case 1: return launch_tb<128>(a, st);
+    case 2: return launch_wide<6>(a, st);
+    case 3: return launch_wide<8>(a, st);
+    default: return launch_wide<10>(a, st);
+  }
 }
 
 }  // namespace prc

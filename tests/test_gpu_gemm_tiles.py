@@ -33,6 +33,13 @@ CASES = [
     ("tiles_one_token_tile", 6, 72, 8, 128, 2, 3, 8, 250, 0),
     ("tiles_three_paged", 150, 136, 4, 128, 2, 3, 16, 50, 128),
     ("tiles_128_ragged", 500, 264, 8, 128, 2, 8, 16, 5, 0),
+    # 256-token tiles of 96, 128 and 160 columns: one, two and five stages of k
+    # with tails, last token and column tiles partial, both head dims.
+    ("wide_96_one_stage", 2100, 40, 8, 128, 2, 8, 16, 1, 0),
+    ("wide_96_d64_paged", 2100, 264, 9, 64, 1, 5, 8, 100, 64),
+    ("wide_128_d64", 3000, 72, 19, 64, 1, 25, 8, 60000, 0),
+    ("wide_128_paged", 2100, 264, 12, 128, 2, 4, 64, 7, 256),
+    ("wide_160", 4097, 72, 8, 128, 2, 8, 16, 0, 0),
     ("tiles_d64", 700, 104, 6, 64, 1, 3, 64, 0, 64),
 ]
 
