@@ -437,7 +437,17 @@ PRC_API prc_status project_kv_and_lr_cache_paged(const uint16_t* X, int64_t T, i
 
 namespace {
 
-size_t workspace_size(const lrsa_dims* dims, bool paged, bool tile_cache = true) {
+// Partials of a chunk that runs as a decode (0: it does not).
+size_t chunk_decode_bytes(const lrsa_dims* dims, int rank, int cus, int* n_splits) {
+  const int group = dims->n_q_heads / dims->n_kv_heads;
+  if (!prc::decode_takes_chunk(dims->n_tok, group)) return 0;
+  prc::decode_plan(dims->s_cap, dims->batch, dims->n_kv_heads, group, dims->head_dim, rank, false, true, cus, n_splits);
+  return prc::decode_workspace_bytes(dims->batch * dims->n_tok, dims->n_q_heads, *n_splits, dims->head_dim, rank);
+}
+
+// `optional`: with the parts a call can do without (tile cache, the partials
+// of a chunk run as a decode).
+size_t workspace_size(const lrsa_dims* dims, bool paged, bool optional = true) {
   if (dims == nullptr || dims->n_tok < 1 || dims->batch < 1 || dims->n_kv_heads < 1 || dims->s_cap < 1 ||
       dims->n_q_heads < dims->n_kv_heads)
     return 0;
@@ -453,7 +463,11 @@ size_t workspace_size(const lrsa_dims* dims, bool paged, bool tile_cache = true)
     prc::prefill_plan(dims->n_tok, group, dims->n_kv_heads, dims->batch, dims->s_cap, plan_cus(), &splits);
     const size_t parts =
         prc::prefill_workspace_bytes(dims->batch, dims->n_tok, dims->n_q_heads, splits, dims->head_dim, r);
-    if (tile_cache && !paged && rank_ok(dims->rank) &&
+    if (optional) {
+      int ns = 0;
+      if (const size_t dec = chunk_decode_bytes(dims, r, plan_cus(), &ns)) return dec > parts ? dec : parts;
+    }
+    if (optional && !paged && rank_ok(dims->rank) &&
         prc::prefill_uses_tile_cache(dims->n_tok, group, dims->head_dim, dims->rank, true, true, paged)) {
       const size_t cache = prc::prefill_tile_cache_bytes(dims->batch, dims->n_kv_heads, dims->s_cap);
       if (cache > 0) return (parts + 255) / 256 * 256 + cache;
@@ -505,6 +519,21 @@ prc_status attention_impl(const char* who, const lrsa_dims* dims, const lrsa_pag
     return launch_status(prc::launch_decode(a, st), what);
   }
   const int plan_cu = plan_cus();
+  // A chunk of a few tokens runs as a decode when the workspace holds its
+  // partials; otherwise as any prefill.
+  int chunk_splits = 0;
+  const size_t chunk = chunk_decode_bytes(dims, a.rank, plan_cu, &chunk_splits);
+  if (chunk > 0 && workspace != nullptr && workspace_bytes >= chunk && aligned(workspace, 16)) {
+    int cus = 0;
+    if (prc_status ds = device_ready(&cus)) return ds;
+#if PRC_DEVICE_CHECKS
+    if (prc_status dc = device_data_check(who, positions, kv_len, a.batch, a.n_tok, a.s_cap, st)) return dc;
+#endif
+    a.n_splits = chunk_splits;
+    a.ws = static_cast<float*>(workspace);
+    snprintf(what, sizeof(what), "%s (prefill)", who);
+    return launch_status(prc::launch_decode(a, st), what);
+  }
   prc::prefill_plan(a.n_tok, a.group, a.n_kv, a.batch, a.s_cap, plan_cu, &a.pf_splits);
   // Split partials first (required when the plan splits), then the tile
   // cache, taken when the workspace has room for it (a smaller or absent
@@ -589,13 +618,16 @@ PRC_API prc_status lr_shared_attention_noalloc(const lrsa_dims* dims, const uint
     return fail(PRC_EWORKSPACE, "the call needs %zu bytes of split partials, above the %zu-byte static workspace",
                 need, kStaticWsBytes);
   void* ws = nullptr;
-  if (need > 0) {
+  int chunk_splits = 0;
+  const size_t chunk = chunk_decode_bytes(dims, c.a.rank, plan_cus(), &chunk_splits);
+  const bool use_ws = need > 0 || (chunk > 0 && chunk <= kStaticWsBytes);
+  if (use_ws) {
     int cus = 0;
     if (prc_status ds = device_ready(&cus)) return ds;
     if (prc_status ss = static_workspace(&ws)) return ss;
   }
   return attention_impl("lr_shared_attention_noalloc", dims, nullptr, Q, K_base, V_base, L_k, L_v, B_k, B_v,
-                        positions, kv_len, O, lse, ws, need > 0 ? kStaticWsBytes : 0, stream);
+                        positions, kv_len, O, lse, ws, use_ws ? kStaticWsBytes : 0, stream);
 }
 
 PRC_API size_t lr_shared_attention_paged_workspace_size(const lrsa_dims* dims) { return workspace_size(dims, true); }

@@ -75,6 +75,10 @@ bool decode_shares_base(int batch, int64_t kv_req_stride);
 // into at most that many.
 void decode_plan(int64_t s_cap, int batch, int n_kv, int group, int head_dim, int rank, bool shared_base, bool paged,
                  int cus, int* n_splits);
+// Whether a prefill of this shape runs as a decode with several tokens (given
+// the workspace for its partials: batch * n_tok rows).  It never shares a base
+// between requests, and plans as paged calls do.
+bool decode_takes_chunk(int n_tok, int group);
 size_t decode_workspace_bytes(int batch, int n_q, int n_splits, int head_dim, int rank);
 hipError_t launch_decode(const AttnArgs& a, hipStream_t stream);
 

@@ -108,6 +108,19 @@ __device__ __forceinline__ int visible_keys(const AttnArgs& a, int r) {
   const int64_t vis = pos + 1 < kvl ? pos + 1 : kvl;
   return vis < 0 ? 0 : (int)vis;
 }
+// The same for a request of several query tokens (at most 16): lane l reads its
+// own column's token; returns the furthest end, `mine` this lane's.
+__device__ __forceinline__ int request_visible_keys(const AttnArgs& a, int b, int tok, int& mine) {
+  int64_t kvl = a.kv_len[b];
+  kvl = kvl < 0 ? 0 : (kvl > a.s_cap ? a.s_cap : kvl);
+  const int64_t pos = a.positions[(int64_t)b * a.n_tok + tok];
+  const int64_t v = pos + 1 < kvl ? pos + 1 : kvl;
+  mine = v < 0 ? 0 : (int)v;
+  int vis = mine;
+#pragma unroll
+  for (int x = 1; x < 16; x <<= 1) vis = max(vis, __shfl_xor(vis, x, 64));
+  return __builtin_amdgcn_readfirstlane(vis);
+}
 // KV tiles per split over `vis` visible keys.  The host plan sizes the grid
 // and the workspace for the caches' capacity (it cannot read kv_len); the
 // splits themselves divide the keys in use, so a cache reserved far beyond
@@ -250,10 +263,14 @@ constexpr int kStageLoads = D / 32 + Ex<R>::NC + RCH(R) + Dec<D, R>::NVD;
 
 // PAGED: the caches are pools reached through block tables (a separate
 // instantiation, so the contiguous kernel carries none of the walk's state).
-template <int D, int R, bool PAGED>
-__global__ void __launch_bounds__(dec_nw(D, R, PAGED) * 64, dec_nw(D, R, PAGED) / 4)
+// MT: several query tokens per request, n_tok * G <= 16: column c of the score
+// result is head c % G of token c / G, each with its own last visible key.
+// (It always takes the register-staged form, so that contiguous and paged
+// calls cut the same splits and agree bit for bit.)
+template <int D, int R, bool PAGED, bool MT>
+__global__ void __launch_bounds__(dec_nw(D, R, PAGED || MT) * 64, dec_nw(D, R, PAGED || MT) / 4)
 lrsa_decode_kernel(const AttnArgs a) {
-  constexpr bool VD = dec_vdma(D, R, PAGED);
+  constexpr bool VD = dec_vdma(D, R, PAGED || MT);
   using C = Dec<D, R, VD>;
   constexpr int NW = C::NW, NT = C::NT;
   __shared__ float2 cs_lds[2][TK * C::CS_ROW];
@@ -282,12 +299,16 @@ lrsa_decode_kernel(const AttnArgs a) {
             has_lk && active, lane);
 
   // This split's share of the keys the request may see.
-  const int vis = visible_keys(a, b);
+  const int n_col = MT ? a.n_tok * G : G;       // columns in use
+  const int tok = MT && c16 < n_col ? c16 / G : 0;  // this lane's query token
+  int vis_col = 0;                              // keys this lane's column may see (MT)
+  const int vis = MT ? request_visible_keys(a, b, tok, vis_col) : visible_keys(a, b);
   const int st_tiles = tiles_per_split(vis, a.n_splits);
   const int64_t t_begin = (int64_t)split * st_tiles * TK;
   if (split > 0 && t_begin >= vis) return;  // past the end (uniform over the workgroup)
   int64_t t_end = t_begin + (int64_t)st_tiles * TK;
   if (t_end > vis) t_end = vis;
+  const int64_t t_end_col = MT && vis_col < t_end ? vis_col : t_end;
   const int n_tiles = t_end > t_begin ? (int)((t_end - t_begin + TK - 1) / TK) : 0;
 
   // RoPE table entries this thread builds every tile, by angle addition from
@@ -325,8 +346,8 @@ lrsa_decode_kernel(const AttnArgs a) {
   // Q^T of the group as the B operand (cols = q heads, zero past G).
   bf16x8 qf[C::NCH];
   {
-    const bool ok = active && c16 < G;
-    const uint16_t* qp = a.Q + ((int64_t)b * a.n_tok * a.n_q + (int64_t)g * G + c16) * D;
+    const bool ok = active && c16 < n_col;
+    const uint16_t* qp = a.Q + (((int64_t)b * a.n_tok + tok) * a.n_q + (int64_t)g * G + (MT ? c16 - tok * G : c16)) * D;
 #pragma unroll
     for (int kk = 0; kk < C::NCH; ++kk) qf[kk] = as_bf16x8(ld16(qp + chunk_dim<D>(kk, q), ok));
   }
@@ -480,7 +501,7 @@ lrsa_decode_kernel(const AttnArgs a) {
       // ---- online softmax: lane l%16 is a head, 4 tokens per lane ---------
       float s2[4];
       float mx = -INFINITY;
-      const int64_t left = t_end - ts;  // visible tokens from ts on
+      const int64_t left = t_end_col - ts;  // visible tokens from ts on
       const int n_vis = left < 0 ? 0 : (left < 16 ? (int)left : 16);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
@@ -544,9 +565,10 @@ tiles_done:
   // l, l^16, l^32, l^48 share it and hold different dims of O^T.
   l_part += shfl_xor(l_part, 16);
   l_part += shfl_xor(l_part, 32);
-  if (c16 >= G) return;
+  if (c16 >= n_col) return;
   const int64_t hstride = (int64_t)a.n_splits * C::PS;
-  float* wsb = a.ws + ((int64_t)b * a.n_q + (int64_t)g * G + c16) * hstride + (int64_t)split * C::PS;
+  float* wsb = a.ws + (((int64_t)b * a.n_tok + tok) * a.n_q + (int64_t)g * G + (MT ? c16 - tok * G : c16)) * hstride +
+               (int64_t)split * C::PS;
   if (q == 0) {
     wsb[0] = m_run;
     wsb[1] = l_part;
@@ -566,7 +588,10 @@ tiles_done:
 __device__ __forceinline__ int splits_written(const AttnArgs& a, int b) {
   if (a.dec_group == 0) return a.n_splits;
   int mine;
-  const int vis = a.dec_group == 1 ? visible_keys(a, b) : group_visible_keys(a, b, a.dec_group, threadIdx.x & 63, mine);
+  const int lane = threadIdx.x & 63;
+  const int vis = a.n_tok > 1      ? request_visible_keys(a, b, (lane & 15) < a.n_tok ? lane & 15 : 0, mine)
+                  : a.dec_group == 1 ? visible_keys(a, b)
+                                     : group_visible_keys(a, b, a.dec_group, lane, mine);
   const int tiles = (vis + TK - 1) / TK, st = tiles_per_split(vis, a.n_splits);
   const int ns = (tiles + st - 1) / st;
   return ns < 1 ? 1 : ns;
@@ -1172,15 +1197,16 @@ hipError_t launch_merge_t(const AttnArgs& a, hipStream_t st) {
 template <int D, int R>
 hipError_t launch_t(AttnArgs a, hipStream_t st) {
   a.dec_group = 1;
-  if (a.kv_tbl != nullptr) {
-    constexpr int nw = dec_nw(D, R, true);
+  const auto go = [&](auto paged, auto mt) {
+    constexpr bool P = decltype(paged)::value, M = decltype(mt)::value;
+    constexpr int nw = dec_nw(D, R, P || M);
     const dim3 grid(a.n_splits, (a.n_kv + nw - 1) / nw, a.batch);
-    hipLaunchKernelGGL((lrsa_decode_kernel<D, R, true>), grid, dim3(64 * nw), 0, st, a);
-  } else {
-    constexpr int nw = dec_nw(D, R, false);
-    const dim3 grid(a.n_splits, (a.n_kv + nw - 1) / nw, a.batch);
-    hipLaunchKernelGGL((lrsa_decode_kernel<D, R, false>), grid, dim3(64 * nw), 0, st, a);
-  }
+    hipLaunchKernelGGL((lrsa_decode_kernel<D, R, P, M>), grid, dim3(64 * nw), 0, st, a);
+  };
+  const std::true_type yes{};
+  const std::false_type no{};
+  if (a.kv_tbl != nullptr) a.n_tok > 1 ? go(yes, yes) : go(yes, no);
+  else a.n_tok > 1 ? go(no, yes) : go(no, no);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   return launch_merge_t<D, R>(a, st);
@@ -1274,6 +1300,13 @@ void decode_plan(int64_t s_cap, int batch, int n_kv, int group, int head_dim, in
   *n_splits = (int)ns;
 }
 
+// A chunk of a few query tokens whose (token, head) pairs per KV head fit the
+// decode's 16 columns runs as a decode: split over the keys as far as the chip
+// is wide, where a prefill would give one workgroup per KV head (times at most
+// eight splits) 256 rows to fill with 16.  (16 tokens over 528 keys, 4 heads of
+// dim 64, rank 8: 20.9 us as a prefill, 10.8 us so, 6.4 of them the decode.)
+bool decode_takes_chunk(int n_tok, int group) { return n_tok > 1 && n_tok * group <= 16; }
+
 size_t decode_workspace_bytes(int batch, int n_q, int n_splits, int head_dim, int rank) {
   return (size_t)batch * n_q * n_splits * (4 + head_dim + rank) * sizeof(float);
 }
@@ -1287,7 +1320,7 @@ hipError_t launch_split_merge(const AttnArgs& a, hipStream_t st) {
 hipError_t launch_decode(const AttnArgs& a, hipStream_t st) {
   // Paged caches go through the per-request kernel (requests may share some
   // blocks and not others).
-  const bool shared = a.kv_tbl == nullptr && decode_shares_base(a.batch, a.kv_stride);
+  const bool shared = a.kv_tbl == nullptr && a.n_tok == 1 && decode_shares_base(a.batch, a.kv_stride);
   if (a.head_dim == 64) return launch_r<64>(a, st, shared);
   if (a.head_dim == 128) return launch_r<128>(a, st, shared);
   return hipErrorInvalidValue;
