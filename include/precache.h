@@ -229,6 +229,10 @@ typedef struct lrsa_dims {
  *              query rows x KV head x request) fill the device's CUs so
  *              unevenly that splitting the KV tiles 2-8 ways shortens the
  *              modelled time (rounds of one unit per CU) by at least 10%.
+ *              For a chunk of at most 16 (token, head) pairs per KV head
+ *              (n_tok * n_q / n_kv <= 16) the size covers partials that let it
+ *              run as a decode, split over the keys; given less, or NULL, it
+ *              runs as any other prefill.
  *              For a prefill of rank 8, 16, 32 or 64 with at least 8 row
  *              tiles (256 query rows each) per KV head, d = 128 and
  *              contiguous caches, the size also covers an optional tile

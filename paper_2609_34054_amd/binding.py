@@ -3,12 +3,15 @@
 Every step of the hot path runs in the library's HIP kernels.  These wrappers
 take torch tensors for device memory and torch's current stream, derive the
 sizes and strides the C ABI wants, and raise :class:`PrecacheError` on any
-non-OK status.  There is no fallback: if the library is missing, the call
+non-OK status.  For plain valid calls that work is done by the native module
+``_marshal`` (1 us a call instead of 10 to 17); whatever it does not recognise
+comes back to the checks here, which raise the error.  There is no fallback: if the library is missing, the call
 fails.
 """
 from __future__ import annotations
 
 import ctypes
+import importlib
 import os
 
 import torch
@@ -117,6 +120,37 @@ def lib() -> ctypes.CDLL:
     return _LIBS[path]
 
 
+class _Native:
+    """The marshalling module and the addresses of a library's entry points."""
+
+    def __init__(self, L):
+        self.m = importlib.import_module("._marshal", __package__)
+        for name in EXPORTS:
+            setattr(self, name, ctypes.cast(getattr(L, name), ctypes.c_void_p).value)
+
+
+_NATIVE: dict = {}
+
+
+def _native() -> _Native:
+    path = CHECKED_LIB_PATH if _CHECKED else LIB_PATH
+    nat = _NATIVE.get(path)
+    if nat is None:
+        nat = _NATIVE[path] = _Native(lib())
+    return nat
+
+
+def _raw_stream(stream) -> int:
+    """Address of `stream`, or of torch's current stream."""
+    if stream is None:
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return int(stream.cuda_stream) if hasattr(stream, "cuda_stream") else int(stream)
+
+
+def _on_gpu(t) -> bool:
+    return type(t) is torch.Tensor and t.is_cuda
+
+
 def _check(func: str, status: int) -> None:
     if status != 0:
         raise PrecacheError(func, status, lib().prc_last_error().decode())
@@ -159,6 +193,14 @@ def precompute_lr_cache(X, A_stack, n_proj: int, n_agents: int, rank: int, L_out
     ``X [T, d_in]`` bf16 (row stride may exceed d_in), ``A_stack [d_in, n_proj*N*r]``,
     ``L_out [n_proj, N, s_cap, r]`` bf16 contiguous.
     """
+    if _on_gpu(X):
+        nat = _native()
+        st = nat.m.project(nat.precompute_lr_cache, X, None, A_stack, 0, 0, n_proj, n_agents, rank, None, None, L_out,
+                           0.0, tok_offset, _raw_stream(stream))
+        if st is not None:
+            if st:
+                _check("precompute_lr_cache", st)
+            return L_out
     _bf16("X", X, 2)
     _bf16("A_stack", A_stack, 2)
     _bf16("L_out", L_out, 4)
@@ -185,6 +227,14 @@ def project_kv_and_lr_cache(X, W, A_stack, n_kv_heads: int, head_dim: int, n_pro
     ``A_stack [d_in, n_proj*N*r]``; ``K_base, V_base [s_cap, n_kv, d]`` and
     ``L_out [n_proj, N, s_cap, r]`` bf16 contiguous, rows ``tok_offset ..`` written.
     """
+    if _on_gpu(X) and W is not None:
+        nat = _native()
+        st = nat.m.project(nat.project_kv_and_lr_cache, X, W, A_stack, n_kv_heads, head_dim, n_proj, n_agents, rank,
+                           K_base, V_base, L_out, rope_theta, tok_offset, _raw_stream(stream))
+        if st is not None:
+            if st:
+                _check("project_kv_and_lr_cache", st)
+            return K_base, V_base, L_out
     _bf16("X", X, 2)
     _bf16("W", W, 2)
     _bf16("A_stack", A_stack, 2)
@@ -221,6 +271,15 @@ def project_kv_and_lr_cache_paged(X, W, A_stack, n_kv_heads: int, head_dim: int,
     ``L_pool [n_proj, N, n_blocks, blk, r]`` (None without LR planes);
     ``block_table [max_blocks]`` int32, contiguous.
     """
+    if _on_gpu(X):
+        nat = _native()
+        st = nat.m.project_paged(nat.project_kv_and_lr_cache_paged, X, W, A_stack, n_kv_heads, head_dim, n_proj,
+                                 n_agents, rank, K_pool, V_pool, L_pool, block_table, rope_theta, tok_offset,
+                                 _raw_stream(stream))
+        if st is not None:
+            if st:
+                _check("project_kv_and_lr_cache_paged", st)
+            return K_pool, V_pool, L_pool
     _bf16("X", X, 2)
     _bf16("W", W, 2)
     _bf16("A_stack", A_stack, 2)
@@ -281,6 +340,15 @@ def paged_workspace_size(dims: LrsaDims) -> int:
     return int(lib().lr_shared_attention_paged_workspace_size(ctypes.byref(dims)))
 
 
+def _outputs(Q, O, lse, want_lse: bool):
+    """The outputs given, or new ones."""
+    if O is None:
+        O = torch.empty_like(Q)
+    if lse is None and want_lse:
+        lse = torch.empty(Q.shape[:3], dtype=torch.float32, device=Q.device)
+    return O, lse
+
+
 def lr_shared_attention(Q, K_base, V_base, L_k, L_v, B_k, B_v, positions, kv_len, *, rope_theta: float,
                         softmax_scale: float = 0.0, O=None, lse=None, want_lse: bool = False,
                         workspace=None, tile_cache: bool = True, stream=None):
@@ -294,6 +362,22 @@ def lr_shared_attention(Q, K_base, V_base, L_k, L_v, B_k, B_v, positions, kv_len
     (the size the paged query reports), so the call rebuilds every tile.
     Returns ``(O, lse)`` (``lse`` None unless requested).
     """
+    if _on_gpu(Q) and Q.dim() == 4:
+        nat = _native()
+        out, out_lse = _outputs(Q, O, lse, want_lse)
+        size = (nat.lr_shared_attention_workspace_size if tile_cache
+                else nat.lr_shared_attention_paged_workspace_size)
+        raw, ws = _raw_stream(stream), workspace
+        while True:
+            st = nat.m.attention(nat.lr_shared_attention, size, False, not tile_cache, Q, K_base, V_base, L_k, L_v, B_k,
+                                 B_v, positions, kv_len, rope_theta, softmax_scale, out, out_lse, ws, raw)
+            if type(st) is not tuple:
+                break
+            ws = torch.empty(st[0], dtype=torch.uint8, device=Q.device)
+        if st is not None:
+            if st:
+                _check("lr_shared_attention", st)
+            return out, out_lse
     for name, t, nd in (("Q", Q, 4), ("K_base", K_base, 4), ("V_base", V_base, 4), ("L_k", L_k, 3),
                         ("L_v", L_v, 3), ("B_k", B_k, 3), ("B_v", B_v, 3)):
         _bf16(name, t, nd)
@@ -337,6 +421,14 @@ def lr_shared_attention_noalloc(Q, K_base, V_base, L_k, L_v, B_k, B_v, positions
     """:func:`lr_shared_attention` through the entry point that allocates nothing:
     the caller preallocates ``O`` (and ``lse``); split partials go to the
     library's static per-device workspace."""
+    if _on_gpu(Q):
+        nat = _native()
+        st = nat.m.attention(nat.lr_shared_attention_noalloc, 0, True, False, Q, K_base, V_base, L_k, L_v, B_k, B_v,
+                             positions, kv_len, rope_theta, softmax_scale, O, lse, None, _raw_stream(stream))
+        if st is not None:
+            if st:
+                _check("lr_shared_attention_noalloc", st)
+            return O, lse
     for name, t, nd in (("Q", Q, 4), ("K_base", K_base, 4), ("V_base", V_base, 4), ("L_k", L_k, 3),
                         ("L_v", L_v, 3), ("B_k", B_k, 3), ("B_v", B_v, 3), ("O", O, 4)):
         _bf16(name, t, nd)
@@ -397,6 +489,21 @@ def lr_shared_attention_paged(Q, K_pool, V_pool, L_k, L_v, B_k, B_v, positions, 
     ``B_k, B_v [B|1, r, n_kv*d]``; ``kv_block_table`` (and ``lr_block_table``,
     default: the same) ``[B, max_blocks]`` int32.
     """
+    if _on_gpu(Q) and Q.dim() == 4:
+        nat = _native()
+        out, out_lse = _outputs(Q, O, lse, want_lse)
+        raw, ws = _raw_stream(stream), workspace
+        while True:
+            st = nat.m.paged(nat.lr_shared_attention_paged, nat.lr_shared_attention_paged_workspace_size, Q, K_pool,
+                             V_pool, L_k, L_v, B_k, B_v, positions, kv_len, kv_block_table, lr_block_table, rope_theta,
+                             softmax_scale, out, out_lse, ws, raw)
+            if type(st) is not tuple:
+                break
+            ws = torch.empty(st[0], dtype=torch.uint8, device=Q.device)
+        if st is not None:
+            if st:
+                _check("lr_shared_attention_paged", st)
+            return out, out_lse
     for name, t in (("K_pool", K_pool), ("V_pool", V_pool), ("L_k", L_k), ("L_v", L_v)):
         if t is not None:
             _bf16(name, t, t.dim())

@@ -4,7 +4,8 @@ Usage: ``python -m paper_2609_34054_amd.build`` or ``build()`` from Python.
 Every call recompiles all sources (objects go to ``_build/``), then links
 ``paper_2609_34054_amd/libprecache.so`` and its checked twin
 ``libprecache_checked.so`` (the same kernels; the ABI layer compiled with
-``PRC_DEVICE_CHECKS=1`` checks device-resident kv_len and positions).
+``PRC_DEVICE_CHECKS=1`` checks device-resident kv_len and positions), and the
+binding's argument marshalling ``_marshal.so``.
 """
 from __future__ import annotations
 
@@ -21,6 +22,7 @@ INCLUDE = os.path.join(ROOT, "include")
 BUILD_DIR = os.path.join(ROOT, "_build")
 LIB_PATH = os.path.join(PKG, "libprecache.so")
 CHECKED_LIB_PATH = os.path.join(PKG, "libprecache_checked.so")
+MARSHAL_PATH = os.path.join(PKG, "_marshal.so")
 
 SOURCES = [
     "abi.cpp",
@@ -93,14 +95,38 @@ def _link(hipcc: str, objs: list[str], path: str, verbose: bool) -> None:
         print(f"built {path}", flush=True)
 
 
+def _build_marshal(verbose: bool) -> None:
+    """The binding's native argument marshalling, a CPython extension against
+    torch's headers (host code only)."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension as ce
+    tmp = MARSHAL_PATH + ".tmp"
+    inc = [a for p in (*ce.include_paths(), sysconfig.get_paths()["include"]) for a in ("-isystem", p)]
+    lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", f"-I{INCLUDE}", *inc,
+           os.path.join(CSRC, "marshal.cpp"), "-o", tmp, f"-L{lib}", "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError(f"g++ failed on marshal.cpp:\n{res.stdout}{res.stderr}")
+    os.replace(tmp, MARSHAL_PATH)
+
+
 def build(verbose: bool = False, jobs: int | None = None) -> str:
-    """Compile every source, link both libraries; returns the release path."""
+    """Compile every source, link both libraries and the binding's marshalling;
+    returns the release path."""
     hipcc = _hipcc()
     os.makedirs(BUILD_DIR, exist_ok=True)
     units = [(s, False) for s in SOURCES] + [("abi.cpp", True)]
     jobs = jobs or min(len(units), max(1, min(8, os.cpu_count() or 1)))
     with cf.ThreadPoolExecutor(max_workers=jobs) as ex:
+        marshal = ex.submit(_build_marshal, verbose)
         objs = list(ex.map(lambda u: _compile(u[0], hipcc, verbose, u[1]), units))
+    marshal.result()
     release, abi_checked = objs[:len(SOURCES)], objs[-1]
     _link(hipcc, release, LIB_PATH, verbose)
     _link(hipcc, [abi_checked if s == "abi.cpp" else o for s, o in zip(SOURCES, release)], CHECKED_LIB_PATH, verbose)

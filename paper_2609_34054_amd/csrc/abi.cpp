@@ -95,9 +95,23 @@ prc_status device_ready(int* cus) {
   return PRC_OK;
 }
 
-prc_status launch_status(hipError_t e, const char* what) {
-  if (e != hipSuccess) return fail(PRC_ELAUNCH, "%s: HIP launch failed: %s", what, hipGetErrorString(e));
+prc_status launch_status(hipError_t e, const char* who, const char* part = "") {
+  if (e != hipSuccess) return fail(PRC_ELAUNCH, "%s%s: HIP launch failed: %s", who, part, hipGetErrorString(e));
   return ok();
+}
+
+// RoPE frequencies omega_j = theta^(-2j/d), as revolutions per position
+// omega_j / (2 pi) in fp64: 64 calls of pow, kept per thread for the last
+// (theta, d), which a program does not change from call to call.
+void rope_frequencies(double theta, int d, double* w2pi) {
+  thread_local double last_theta = 0.0, last[prc::kMaxHalfDim];
+  thread_local int last_d = 0;
+  if (theta != last_theta || d != last_d) {
+    for (int j = 0; j < d / 2; ++j) last[j] = std::pow(theta, -2.0 * j / (double)d) / (2.0 * M_PI);
+    last_theta = theta;
+    last_d = d;
+  }
+  std::memcpy(w2pi, last, sizeof(double) * (size_t)(d / 2));
 }
 
 #if PRC_DEVICE_CHECKS
@@ -253,10 +267,7 @@ prc_status check_attention(const lrsa_dims* dims, const uint16_t* Q, const uint1
   }
   const double scale = d.softmax_scale > 0.f ? (double)d.softmax_scale : 1.0 / std::sqrt((double)d.head_dim);
   a.scale_log2 = (float)(scale * 1.4426950408889634);
-  // RoPE frequencies omega_j = theta^(-2j/d), passed as revolutions per
-  // position, omega_j / (2 pi), in fp64.
-  for (int j = 0; j < d.head_dim / 2; ++j)
-    a.w2pi[j] = std::pow(d.rope_theta, -2.0 * j / (double)d.head_dim) / (2.0 * M_PI);
+  rope_frequencies(d.rope_theta, d.head_dim, a.w2pi);
   return ok();
 }
 
@@ -395,9 +406,7 @@ prc_status project_impl(const char* who, const uint16_t* X, int64_t T, int64_t d
   a.tbl = paged ? tbl : nullptr;
   a.blk = blk;
   a.nblk = n_blocks;
-  if (with_base)
-    for (int j = 0; j < head_dim / 2; ++j)
-      a.w2pi[j] = std::pow(rope_theta, -2.0 * j / (double)head_dim) / (2.0 * M_PI);
+  if (with_base) rope_frequencies(rope_theta, head_dim, a.w2pi);
   int cus = 0;
   if (prc_status ds = device_ready(&cus)) return ds;
   a.cus = cus;
@@ -500,7 +509,6 @@ prc_status attention_impl(const char* who, const lrsa_dims* dims, const lrsa_pag
   if (!rank_ok(dims->rank)) a.rank = 8;
   else a.rank = dims->rank;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  char what[96];
   if (dims->n_tok == 1) {
     const size_t need = workspace_size(dims, pg != nullptr);
     if (workspace == nullptr || workspace_bytes < need)
@@ -515,8 +523,7 @@ prc_status attention_impl(const char* who, const lrsa_dims* dims, const lrsa_pag
     prc::decode_plan(a.s_cap, a.batch, a.n_kv, a.group, a.head_dim, a.rank,
                      pg == nullptr && prc::decode_shares_base(a.batch, a.kv_stride), pg != nullptr, cus, &a.n_splits);
     a.ws = static_cast<float*>(workspace);
-    snprintf(what, sizeof(what), "%s (decode)", who);
-    return launch_status(prc::launch_decode(a, st), what);
+    return launch_status(prc::launch_decode(a, st), who, " (decode)");
   }
   const int plan_cu = plan_cus();
   // A chunk of a few tokens runs as a decode when the workspace holds its
@@ -531,8 +538,7 @@ prc_status attention_impl(const char* who, const lrsa_dims* dims, const lrsa_pag
 #endif
     a.n_splits = chunk_splits;
     a.ws = static_cast<float*>(workspace);
-    snprintf(what, sizeof(what), "%s (prefill)", who);
-    return launch_status(prc::launch_decode(a, st), what);
+    return launch_status(prc::launch_decode(a, st), who, " (prefill)");
   }
   prc::prefill_plan(a.n_tok, a.group, a.n_kv, a.batch, a.s_cap, plan_cu, &a.pf_splits);
   // Split partials first (required when the plan splits), then the tile
@@ -563,8 +569,7 @@ prc_status attention_impl(const char* who, const lrsa_dims* dims, const lrsa_pag
 #if PRC_DEVICE_CHECKS
   if (prc_status dc = device_data_check(who, positions, kv_len, a.batch, a.n_tok, a.s_cap, st)) return dc;
 #endif
-  snprintf(what, sizeof(what), "%s (prefill)", who);
-  return launch_status(prc::launch_prefill(a, st), what);
+  return launch_status(prc::launch_prefill(a, st), who, " (prefill)");
 }
 
 }  // namespace
