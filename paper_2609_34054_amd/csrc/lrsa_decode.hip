@@ -292,15 +292,27 @@ lrsa_decode_kernel(const AttnArgs a) {
   const int G = a.group;
   const int q = lane >> 4, c16 = lane & 15;
   const bool has_lk = a.Lk != nullptr, has_lv = a.Lv != nullptr;
-  // The up-projection rows go out first: their latency hides behind the rest
-  // of the set-up (a split of a small batch covers only a few tiles).
+  // The one-time loads go out first, then (below) the first stages' rows: a
+  // split of a small batch covers only a few tiles, and each of these reads
+  // behind another adds a memory latency to it.
   BtStage<D, R> bts;
   bts.issue(has_lk ? a.Bk + (int64_t)b * a.b_stride + (int64_t)g * D : nullptr, (int64_t)a.n_kv * D,
             has_lk && active, lane);
 
-  // This split's share of the keys the request may see.
   const int n_col = MT ? a.n_tok * G : G;       // columns in use
   const int tok = MT && c16 < n_col ? c16 / G : 0;  // this lane's query token
+  // Q^T of the group as the B operand (cols = q heads, zero past G).
+  bf16x8 qf[C::NCH];
+  {
+    const bool ok = active && c16 < n_col;
+    const uint16_t* qp = a.Q + (((int64_t)b * a.n_tok + tok) * a.n_q + (int64_t)g * G + (MT ? c16 - tok * G : c16)) * D;
+#pragma unroll
+    for (int kk = 0; kk < C::NCH; ++kk) qf[kk] = as_bf16x8(ld16(qp + chunk_dim<D>(kk, q), ok));
+  }
+  // This thread's frequency: of its table entries and of the base angles.
+  static_assert(NT % C::HALF == 0, "one frequency per thread");
+  const double w2pi_t = a.w2pi[tid % C::HALF];
+  // This split's share of the keys the request may see.
   int vis_col = 0;                              // keys this lane's column may see (MT)
   const int vis = MT ? request_visible_keys(a, b, tok, vis_col) : visible_keys(a, b);
   const int st_tiles = tiles_per_split(vis, a.n_splits);
@@ -310,6 +322,36 @@ lrsa_decode_kernel(const AttnArgs a) {
   if (t_end > vis) t_end = vis;
   const int64_t t_end_col = MT && vis_col < t_end ? vis_col : t_end;
   const int n_tiles = t_end > t_begin ? (int)((t_end - t_begin + TK - 1) / TK) : 0;
+
+  const int64_t row = (int64_t)a.n_kv * D;  // elements between tokens
+  // This request's caches (or pools, paged through its rows of the block
+  // tables).
+  const uint16_t* Kb = a.Kb + (int64_t)b * a.kv_stride + (int64_t)g * D;
+  const uint16_t* Vb = a.Vb + (int64_t)b * a.kv_stride + (int64_t)g * D;
+  const uint16_t* Lk = has_lk ? a.Lk + (int64_t)b * a.l_stride : nullptr;
+  const uint16_t* Lv = has_lv ? a.Lv + (int64_t)b * a.l_stride : nullptr;
+  const int64_t t_end_w = active ? t_end : t_begin;  // inactive waves load nothing
+
+  uint16_t* vl = v_lds[w];
+  uint16_t* lvl = lv_lds[w];
+  const StageOffsets<D, R> so = stage_offsets<D, R, VD>(row, lane);
+  Stage<D, R> st[C::NST];
+  // Sub-blocks are loaded in token order, so paged caches are walked with them.
+  PageWalk walk;
+  if constexpr (PAGED)
+    walk.start(a.kv_tbl + (int64_t)b * a.max_blk, a.lr_tbl + (int64_t)b * a.max_blk, a.max_blk, a.blk, a.kv_nblk,
+               a.lr_nblk, t_begin, t_end_w);
+  // Stage `slot` of the ring (VD: also its V buffer in LDS).
+  auto load = [&](Stage<D, R>& s, int64_t t, int slot) {
+    int64_t kr = t, lr = t;
+    if constexpr (PAGED) walk.next(16, t_end_w, kr, lr);
+    stage_load<D, R, VD>(s, so, Kb, Vb, Lk, Lv, kr, lr, row, t, t_end_w, slot == 0 ? vl : v_lds1[VD ? w : 0]);
+  };
+  if constexpr (!VD) {  // (direct V loads wait until their buffers are free and zeroed)
+#pragma unroll
+    for (int p = 0; p < C::PF; ++p) load(st[p], t_begin + 16 * p, p);
+    __builtin_amdgcn_sched_barrier(0);
+  }
 
   // RoPE table entries this thread builds every tile, by angle addition from
   // the exact base angle of the tile and exact per-entry offset angles.
@@ -322,35 +364,16 @@ lrsa_decode_kernel(const AttnArgs a) {
     eidx[k] = tok * C::CS_ROW + ej[k];
     cdl[k] = 1.f;
     sdl[k] = 0.f;
-    if (has_lk) rope_cs(tok, a.w2pi[ej[k]], cdl[k], sdl[k]);
+    if (has_lk) rope_cs(tok, w2pi_t, cdl[k], sdl[k]);
   }
-  // This thread's frequency for the per-tile base angles, read once.
-  const double w2pi_t = a.w2pi[tid < C::HALF ? tid : 0];
   if (has_lk && tid < C::HALF && n_tiles > 0) {
     float c, s;
-    rope_cs((int)t_begin, a.w2pi[tid], c, s);
+    rope_cs((int)t_begin, w2pi_t, c, s);
     base_lds[0][tid] = make_float2(c, s);
   }
   // L_v tile columns past the rank stay zero (rank 8 pads to 16).
   for (int i = lane; i < 16 * C::LV_ROW; i += 64) lv_lds[w][i] = 0;
 
-  const int64_t row = (int64_t)a.n_kv * D;  // elements between tokens
-  // This request's caches (or pools, paged through its rows of the block
-  // tables).
-  const uint16_t* Kb = a.Kb + (int64_t)b * a.kv_stride + (int64_t)g * D;
-  const uint16_t* Vb = a.Vb + (int64_t)b * a.kv_stride + (int64_t)g * D;
-  const uint16_t* Lk = has_lk ? a.Lk + (int64_t)b * a.l_stride : nullptr;
-  const uint16_t* Lv = has_lv ? a.Lv + (int64_t)b * a.l_stride : nullptr;
-  const int64_t t_end_w = active ? t_end : t_begin;  // inactive waves load nothing
-
-  // Q^T of the group as the B operand (cols = q heads, zero past G).
-  bf16x8 qf[C::NCH];
-  {
-    const bool ok = active && c16 < n_col;
-    const uint16_t* qp = a.Q + (((int64_t)b * a.n_tok + tok) * a.n_q + (int64_t)g * G + (MT ? c16 - tok * G : c16)) * D;
-#pragma unroll
-    for (int kk = 0; kk < C::NCH; ++kk) qf[kk] = as_bf16x8(ld16(qp + chunk_dim<D>(kk, q), ok));
-  }
   typename Ex<R>::Frag bkf[C::NBLK][Ex<R>::NC];
   bts.finish(bkf, v_lds[w], lane);
   if constexpr (VD) {
@@ -372,28 +395,15 @@ lrsa_decode_kernel(const AttnArgs a) {
 #pragma unroll
   for (int rc = 0; rc < C::RC; ++rc) accl[rc] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  uint16_t* vl = v_lds[w];
-  uint16_t* lvl = lv_lds[w];
   const int vrow = lane / C::LPR, vdim = (lane % C::LPR) * 8;
   // Transposing-read addresses: lane j of group l/16 reads row
   // 4*(l/16) + (j/4), columns 4*(j%4) .. +3 of a 16-column block.
   const int tr_row = 4 * q + (c16 >> 2), tr_col = 4 * (c16 & 3);
 
-  const StageOffsets<D, R> so = stage_offsets<D, R, VD>(row, lane);
-  Stage<D, R> st[C::NST];
-  // Sub-blocks are loaded in token order, so paged caches are walked with them.
-  PageWalk walk;
-  if constexpr (PAGED)
-    walk.start(a.kv_tbl + (int64_t)b * a.max_blk, a.lr_tbl + (int64_t)b * a.max_blk, a.max_blk, a.blk, a.kv_nblk,
-               a.lr_nblk, t_begin, t_end_w);
-  // Stage `slot` of the ring (VD: also its V buffer in LDS).
-  auto load = [&](Stage<D, R>& s, int64_t t, int slot) {
-    int64_t kr = t, lr = t;
-    if constexpr (PAGED) walk.next(16, t_end_w, kr, lr);
-    stage_load<D, R, VD>(s, so, Kb, Vb, Lk, Lv, kr, lr, row, t, t_end_w, slot == 0 ? vl : v_lds1[VD ? w : 0]);
-  };
+  if constexpr (VD) {
 #pragma unroll
-  for (int p = 0; p < C::PF; ++p) load(st[p], t_begin + 16 * p, p);
+    for (int p = 0; p < C::PF; ++p) load(st[p], t_begin + 16 * p, p);
+  }
 
   __syncthreads();  // base angles of the first tile, zeroed L_v tiles
 
