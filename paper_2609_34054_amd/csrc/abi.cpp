@@ -484,10 +484,20 @@ size_t workspace_size(const lrsa_dims* dims, bool paged, bool optional = true) {
     return parts;
   }
   int n_splits = 0;
-  // Paged caches always take the per-request decode kernel.
+  // Paged caches always take the per-request decode kernel; the size covers
+  // either of its forms (the register-staged one has at least as many splits).
   const bool shared = !paged && prc::decode_shares_base(dims->batch, dims->kv_req_stride);
   prc::decode_plan(dims->s_cap, dims->batch, dims->n_kv_heads, dims->n_q_heads / dims->n_kv_heads, dims->head_dim, r,
                    shared, paged, plan_cus(), &n_splits);
+  if (optional) {
+    // Room for splits balanced over the requests (paged: in the form with the
+    // longer splits, which it takes unless its block tables are very long).
+    int ns = 0;
+    prc::decode_plan(dims->s_cap, dims->batch, dims->n_kv_heads, dims->n_q_heads / dims->n_kv_heads, dims->head_dim, r,
+                     shared, false, plan_cus(), &ns);
+    if (prc::decode_balances(dims->s_cap, dims->batch, dims->n_tok, dims->head_dim, r, ns, shared, false) && 2 * ns > n_splits)
+      n_splits = 2 * ns;
+  }
   return prc::decode_workspace_bytes(dims->batch, dims->n_q_heads, n_splits, dims->head_dim, r);
 }
 
@@ -510,7 +520,7 @@ prc_status attention_impl(const char* who, const lrsa_dims* dims, const lrsa_pag
   else a.rank = dims->rank;
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (dims->n_tok == 1) {
-    const size_t need = workspace_size(dims, pg != nullptr);
+    const size_t need = workspace_size(dims, pg != nullptr, false);
     if (workspace == nullptr || workspace_bytes < need)
       return fail(PRC_EWORKSPACE, "workspace of %zu bytes given, %zu needed", workspace == nullptr ? 0 : workspace_bytes,
                   need);
@@ -521,7 +531,16 @@ prc_status attention_impl(const char* who, const lrsa_dims* dims, const lrsa_pag
     if (prc_status dc = device_data_check(who, positions, kv_len, a.batch, a.n_tok, a.s_cap, st)) return dc;
 #endif
     prc::decode_plan(a.s_cap, a.batch, a.n_kv, a.group, a.head_dim, a.rank,
-                     pg == nullptr && prc::decode_shares_base(a.batch, a.kv_stride), pg != nullptr, cus, &a.n_splits);
+                     pg == nullptr && prc::decode_shares_base(a.batch, a.kv_stride),
+                     pg != nullptr && !prc::decode_direct_paged(a.n_tok, a.max_blk), cus, &a.n_splits);
+    // With room for twice the partials the splits follow the requests' lengths.
+    const bool shared = pg == nullptr && prc::decode_shares_base(a.batch, a.kv_stride);
+    const bool staged = pg != nullptr && !prc::decode_direct_paged(a.n_tok, a.max_blk);
+    if (prc::decode_balances(a.s_cap, a.batch, a.n_tok, a.head_dim, a.rank, a.n_splits, shared, staged) &&
+        workspace_bytes >= prc::decode_workspace_bytes(a.batch, a.n_q, 2 * a.n_splits, a.head_dim, a.rank)) {
+      a.wg_total = a.n_splits * a.batch;
+      a.n_splits *= 2;
+    }
     a.ws = static_cast<float*>(workspace);
     return launch_status(prc::launch_decode(a, st), who, " (decode)");
   }

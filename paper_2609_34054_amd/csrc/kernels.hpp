@@ -50,6 +50,8 @@ struct AttnArgs {
   int32_t head_dim;
   int32_t rank;
   int32_t n_splits;     // splits with room in the workspace per (request, token, head) row
+  int32_t wg_total;     // decode: split workgroups of the whole batch when its splits are
+                        // balanced over the requests' lengths, else 0
   int32_t dec_group;    // decode: consecutive requests whose splits cover the same
                         // ranges (1: each its own); 0: a prefill, whose splits all write
   int32_t pf_splits;    // prefill: KV splits per row tile (1: none)
@@ -69,12 +71,20 @@ int decode_tile_tokens();
 // A decode batch whose requests all read one base cache (request stride 0)
 // runs the shared-base kernel: each base tile is read once for all of them.
 bool decode_shares_base(int batch, int64_t kv_req_stride);
-// `cus`: compute units of the device the call runs on; `paged`: the caches
-// are block pools (the plan follows the kernel form the call takes).  The
+// `cus`: compute units of the device the call runs on; `staged`: the call
+// takes the form with V staged in registers where the rank has two (paged
+// calls with long block tables, several query tokens).  The
 // plan gives the number of splits; the kernels cut each request's keys in use
 // into at most that many.
-void decode_plan(int64_t s_cap, int batch, int n_kv, int group, int head_dim, int rank, bool shared_base, bool paged,
+void decode_plan(int64_t s_cap, int batch, int n_kv, int group, int head_dim, int rank, bool shared_base, bool staged,
                  int cus, int* n_splits);
+// Whether a decode of `n_splits` splits a request cuts them by the requests'
+// lengths, over n_splits * batch workgroups, given room for twice as many
+// partials a row.
+bool decode_balances(int64_t s_cap, int batch, int n_tok, int head_dim, int rank, int n_splits, bool shared_base, bool staged);
+// Whether a paged call's block tables (max_blk entries a request) let it take
+// the form that stages V by direct loads.
+bool decode_direct_paged(int n_tok, int max_blk);
 // Whether a prefill of this shape runs as a decode with several tokens (given
 // the workspace for its partials: batch * n_tok rows).  It never shares a base
 // between requests, and plans as paged calls do.

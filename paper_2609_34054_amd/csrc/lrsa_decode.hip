@@ -53,15 +53,20 @@ constexpr int dec_waves(int rank) { return rank >= 64 ? 4 : 8; }
 // the whole register file leaves room for one more staged sub-block; at two
 // waves per SIMD the extra stage spills and loses.
 constexpr int dec_prefetch(int rank) { return rank >= 64 ? 2 : 1; }
-// Contiguous rank-64 decode at d = 128 instead stages its V rows by direct
-// global->LDS loads, which frees the registers the V stages take: with one
-// sub-block in flight it then fits in 256 registers (251), so it runs 8-wave
-// workgroups, two waves per SIMD, like the lower ranks (64k, 8 requests:
-// 467 -> 440 us).  Paged caches keep the 4-wave form (their walk issues
-// block-table loads between the stages, which the fixed load count of the
-// V wait below does not cover).
-constexpr bool dec_vdma(int d, int rank, bool paged) { return d == 128 && rank == 64 && !paged; }
-constexpr int dec_nw(int d, int rank, bool paged) { return dec_vdma(d, rank, paged) ? 8 : dec_waves(rank); }
+// Rank-64 decode at d = 128 instead stages its V rows by direct global->LDS
+// loads, which frees the registers the V stages take: with one sub-block in
+// flight it then fits in 256 registers (251), so it runs 8-wave workgroups,
+// two waves per SIMD, like the lower ranks (64k, 8 requests: 467 -> 440 us).
+// Paged calls take it too while their block tables are short enough for the
+// split's entries to wait in LDS (a table read from memory between the stages
+// would upset the fixed load count of the V wait below); longer tables, and
+// several query tokens, keep the register-staged 4-wave form (`staged`).
+// Eight paged requests of 65.5k tokens: 462 -> 426 us; of 36.8k-65.5k: 369 us,
+// 410 with equal splits for each request, 345 with balanced ones (below); four
+// of 3000: 43.8 -> 34.0 us.
+constexpr bool dec_vdma(int d, int rank, bool staged) { return d == 128 && rank == 64 && !staged; }
+constexpr int dec_nw(int d, int rank, bool staged) { return dec_vdma(d, rank, staged) ? 8 : dec_waves(rank); }
+constexpr int kLdsBlocks = 2048;  // block-table entries of a split the direct paged form holds in LDS
 constexpr int gcd_c(int a, int b) { return b == 0 ? a : gcd_c(b, a % b); }
 
 template <int D, int R, bool VD = false>
@@ -143,6 +148,37 @@ __device__ __forceinline__ int group_visible_keys(const AttnArgs& a, int b, int 
 #pragma unroll
   for (int x = 1; x < 8; x <<= 1) vis = max(vis, __shfl_xor(vis, x, 64));
   return __builtin_amdgcn_readfirstlane(vis);
+}
+
+// Splits of one length over all requests of a batch (at most 64: lane r holds
+// request r), so that requests of different lengths take workgroups in
+// proportion to their keys: the smallest tiles-per-split for which all splits
+// fit a.wg_total workgroups and each request's fit its a.n_splits places in the
+// workspace.  Every workgroup, and the merge, derive the same cut from the
+// lengths.  Returns tiles per split; `mine` is lane r's number of splits.
+// (Eight requests of 36.8k-65.5k tokens, rank 64, one round of workgroups:
+// 409 us with as many splits for each request, 342 us so; sixteen of 5k-20k,
+// paged: 273 -> 187 us; equal lengths are cut as before.)
+__device__ __forceinline__ int balanced_splits(const AttnArgs& a, int lane, int& mine) {
+  // Over the lanes that hold requests (the next power of two of them).
+  auto sum64 = [&](int v) {
+    for (int x = 1; x < a.batch; x <<= 1) v += __shfl_xor(v, x, 64);
+    return __builtin_amdgcn_readfirstlane(v);
+  };
+  const int tiles = lane < a.batch ? max(1, (visible_keys(a, lane) + TK - 1) / TK) : 0;
+  int longest = tiles;
+  for (int x = 1; x < a.batch; x <<= 1) longest = max(longest, __shfl_xor(longest, x, 64));
+  longest = __builtin_amdgcn_readfirstlane(longest);
+  const int total = sum64(tiles);
+  int st = max((total + a.wg_total - 1) / a.wg_total, (longest + a.n_splits - 1) / a.n_splits);
+  // Rounding up leaves at most one split per request too many: a step of 1/32
+  // reaches a fit within a few turns (wg_total is at least twice the batch).
+  for (;;) {
+    mine = (tiles + st - 1) / st;
+    if (sum64(mine) <= a.wg_total) break;
+    st += st < 64 ? 1 : st / 32;
+  }
+  return st;
 }
 
 // Transposing LDS read: lane j of each 16-lane group points at 4 consecutive
@@ -243,16 +279,64 @@ __device__ __forceinline__ void stage_load(Stage<D, R>& s, const StageOffsets<D,
   for (int rc = 0; rc < C::RC; ++rc)
     s.lv[rc] = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(rlv, o.lr[rc], 0, 0));
   if constexpr (VD) {
+#ifdef __HIP_DEVICE_COMPILE__  // the host pass does not know the 16-byte form
 #pragma unroll
     for (int k = 0; k < C::NVD; ++k)
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rv, (__attribute__((address_space(3))) void*)(vdst + 512 * k), 16,
                                                o.vd[k], 0, 0, 0);
+#endif
   } else {
 #pragma unroll
     for (int iv = 0; iv < C::NVL; ++iv)
       s.v[iv] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rv, o.v[iv], 0, 0));
   }
 }
+
+// The paged walk over block-table entries in LDS: the entries of the block
+// after the current one are read a block ahead.  Entries are clamped into the
+// pools, indexes into the split's entries (past its end nothing is loaded).
+struct LdsWalk {
+  const int32_t *kv, *lr;
+  int n, blk, kv_nblk, lr_nblk, q, rem;
+  int ek, el;            // current block (wave-uniform)
+  int32_t nk, nl;        // entries of the next
+  __device__ __forceinline__ void enter() {
+    ek = __builtin_amdgcn_readfirstlane(nk);
+    el = __builtin_amdgcn_readfirstlane(nl);
+    ek = ek < 0 ? 0 : (ek >= kv_nblk ? kv_nblk - 1 : ek);
+    el = el < 0 ? 0 : (el >= lr_nblk ? lr_nblk - 1 : el);
+    const int i = q + 1 < n ? q + 1 : 0;
+    nk = kv[i];
+    nl = lr[i];
+  }
+  __device__ __forceinline__ void start(const int32_t* kv_, const int32_t* lr_, int n_, int blk_, int kvn, int lrn, int rem_) {
+    kv = kv_;
+    lr = lr_;
+    n = n_;
+    blk = blk_;
+    kv_nblk = kvn;
+    lr_nblk = lrn;
+    q = 0;
+    rem = rem_;
+    nk = nl = 0;
+    if (n > 0) {
+      nk = kv[0];
+      nl = lr[0];
+    }
+    enter();
+  }
+  // Pool rows (base, LR) of the next sub-block's first token; then step on.
+  __device__ __forceinline__ void next(int step, int64_t& kv_row, int64_t& lr_row) {
+    kv_row = (int64_t)ek * blk + rem;
+    lr_row = (int64_t)el * blk + rem;
+    rem += step;
+    if (rem == blk) {
+      rem = 0;
+      ++q;
+      enter();
+    }
+  }
+};
 
 // s_waitcnt with vmcnt(n) and no wait on the other counters.
 constexpr int vmcnt_imm(int n) { return (n & 0xF) | ((n >> 4) << 14) | 0x0F70; }
@@ -267,10 +351,11 @@ constexpr int kStageLoads = D / 32 + Ex<R>::NC + RCH(R) + Dec<D, R>::NVD;
 // result is head c % G of token c / G, each with its own last visible key.
 // (It always takes the register-staged form, so that contiguous and paged
 // calls cut the same splits and agree bit for bit.)
-template <int D, int R, bool PAGED, bool MT>
-__global__ void __launch_bounds__(dec_nw(D, R, PAGED || MT) * 64, dec_nw(D, R, PAGED || MT) / 4)
+template <int D, int R, bool PAGED, bool MT, bool STAGED = PAGED || MT>
+__global__ void __launch_bounds__(dec_nw(D, R, STAGED) * 64, dec_nw(D, R, STAGED) / 4)
 lrsa_decode_kernel(const AttnArgs a) {
-  constexpr bool VD = dec_vdma(D, R, PAGED || MT);
+  constexpr bool VD = dec_vdma(D, R, STAGED);
+  constexpr bool LW = PAGED && VD;  // the table walk reads LDS
   using C = Dec<D, R, VD>;
   constexpr int NW = C::NW, NT = C::NT;
   __shared__ float2 cs_lds[2][TK * C::CS_ROW];
@@ -282,11 +367,26 @@ lrsa_decode_kernel(const AttnArgs a) {
   __shared__ __attribute__((aligned(16))) uint16_t v_lds[NW][VD ? C::VST : 16 * C::V_ROW];
   __shared__ __attribute__((aligned(16))) uint16_t v_lds1[VD ? NW : 1][VD ? C::VST : 8];
   __shared__ __attribute__((aligned(16))) uint16_t lv_lds[NW][16 * C::LV_ROW];
+  __shared__ int32_t tbl_lds[2][LW ? kLdsBlocks : 1];  // this split's base and LR block-table entries
 
   // The wave index is made visibly wave-uniform, so that everything derived
   // from it (the KV head and its buffer resources) lives in scalar registers.
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int split = blockIdx.x, b = blockIdx.z;
+  int split = blockIdx.x, b = blockIdx.z, st_bal = 0;
+  if (VD && a.wg_total > 0) {
+    // Workgroup x takes the x-th split of the batch, request by request.
+    int mine;
+    st_bal = balanced_splits(a, lane, mine);
+    int end = mine;  // splits of requests 0 .. lane
+    for (int x = 1; x < a.batch; x <<= 1) {
+      const int o = __shfl_up(end, x, 64);
+      if (lane >= x) end += o;
+    }
+    const uint64_t past = __ballot(lane < a.batch && end <= (int)blockIdx.x);  // requests wholly before this workgroup
+    b = __builtin_popcountll(past);
+    if (b >= a.batch) return;  // uniform over the workgroup
+    split = (int)blockIdx.x - (__builtin_amdgcn_readlane(end, b) - __builtin_amdgcn_readlane(mine, b));
+  }
   const int g = blockIdx.y * NW + w;
   const bool active = g < a.n_kv;
   const int G = a.group;
@@ -315,7 +415,7 @@ lrsa_decode_kernel(const AttnArgs a) {
   // This split's share of the keys the request may see.
   int vis_col = 0;                              // keys this lane's column may see (MT)
   const int vis = MT ? request_visible_keys(a, b, tok, vis_col) : visible_keys(a, b);
-  const int st_tiles = tiles_per_split(vis, a.n_splits);
+  const int st_tiles = VD && a.wg_total > 0 ? st_bal : tiles_per_split(vis, a.n_splits);
   const int64_t t_begin = (int64_t)split * st_tiles * TK;
   if (split > 0 && t_begin >= vis) return;  // past the end (uniform over the workgroup)
   int64_t t_end = t_begin + (int64_t)st_tiles * TK;
@@ -338,13 +438,24 @@ lrsa_decode_kernel(const AttnArgs a) {
   Stage<D, R> st[C::NST];
   // Sub-blocks are loaded in token order, so paged caches are walked with them.
   PageWalk walk;
-  if constexpr (PAGED)
+  LdsWalk lwalk;
+  if constexpr (LW) {
+    const int q0 = (int)(t_begin / a.blk), nq = t_end > t_begin ? (int)((t_end - 1) / a.blk) - q0 + 1 : 0;
+    for (int i = tid; i < nq; i += NT) {
+      tbl_lds[0][i] = a.kv_tbl[(int64_t)b * a.max_blk + q0 + i];
+      tbl_lds[1][i] = a.lr_tbl[(int64_t)b * a.max_blk + q0 + i];
+    }
+    __syncthreads();
+    lwalk.start(tbl_lds[0], tbl_lds[1], nq, a.blk, a.kv_nblk, a.lr_nblk, (int)(t_begin - (int64_t)q0 * a.blk));
+  } else if constexpr (PAGED) {
     walk.start(a.kv_tbl + (int64_t)b * a.max_blk, a.lr_tbl + (int64_t)b * a.max_blk, a.max_blk, a.blk, a.kv_nblk,
                a.lr_nblk, t_begin, t_end_w);
+  }
   // Stage `slot` of the ring (VD: also its V buffer in LDS).
   auto load = [&](Stage<D, R>& s, int64_t t, int slot) {
     int64_t kr = t, lr = t;
-    if constexpr (PAGED) walk.next(16, t_end_w, kr, lr);
+    if constexpr (LW) lwalk.next(16, kr, lr);
+    else if constexpr (PAGED) walk.next(16, t_end_w, kr, lr);
     stage_load<D, R, VD>(s, so, Kb, Vb, Lk, Lv, kr, lr, row, t, t_end_w, slot == 0 ? vl : v_lds1[VD ? w : 0]);
   };
   if constexpr (!VD) {  // (direct V loads wait until their buffers are free and zeroed)
@@ -599,6 +710,10 @@ __device__ __forceinline__ int splits_written(const AttnArgs& a, int b) {
   if (a.dec_group == 0) return a.n_splits;
   int mine;
   const int lane = threadIdx.x & 63;
+  if (a.wg_total > 0) {
+    balanced_splits(a, lane, mine);
+    return __builtin_amdgcn_readlane(mine, b);
+  }
   const int vis = a.n_tok > 1      ? request_visible_keys(a, b, (lane & 15) < a.n_tok ? lane & 15 : 0, mine)
                   : a.dec_group == 1 ? visible_keys(a, b)
                                      : group_visible_keys(a, b, a.dec_group, lane, mine);
@@ -1207,10 +1322,19 @@ hipError_t launch_merge_t(const AttnArgs& a, hipStream_t st) {
 template <int D, int R>
 hipError_t launch_t(AttnArgs a, hipStream_t st) {
   a.dec_group = 1;
+  const unsigned gx = a.wg_total > 0 ? a.wg_total : a.n_splits, gz = a.wg_total > 0 ? 1 : a.batch;
   const auto go = [&](auto paged, auto mt) {
     constexpr bool P = decltype(paged)::value, M = decltype(mt)::value;
+    if constexpr (P && !M && dec_vdma(D, R, false)) {
+      if (decode_direct_paged(a.n_tok, a.max_blk)) {
+        constexpr int nw = dec_nw(D, R, false);
+        const dim3 grid(gx, (a.n_kv + nw - 1) / nw, gz);
+        hipLaunchKernelGGL((lrsa_decode_kernel<D, R, P, M, false>), grid, dim3(64 * nw), 0, st, a);
+        return;
+      }
+    }
     constexpr int nw = dec_nw(D, R, P || M);
-    const dim3 grid(a.n_splits, (a.n_kv + nw - 1) / nw, a.batch);
+    const dim3 grid(gx, (a.n_kv + nw - 1) / nw, gz);
     hipLaunchKernelGGL((lrsa_decode_kernel<D, R, P, M>), grid, dim3(64 * nw), 0, st, a);
   };
   const std::true_type yes{};
@@ -1272,7 +1396,20 @@ int decode_tile_tokens() { return TK; }
 
 bool decode_shares_base(int batch, int64_t kv_req_stride) { return batch > 1 && kv_req_stride == 0; }
 
-void decode_plan(int64_t s_cap, int batch, int n_kv, int group, int head_dim, int rank, bool shared_base, bool paged,
+// The one-round kernel has nothing left to even out requests of different
+// lengths with, so batches of 2 to 64 of them cut their splits by length (a
+// request may then take up to twice its even share).  Not where splits are
+// short anyway: the lengths are read before anything else, about 1.5 us in the
+// kernel and the merge.  The two-round kernels gain nothing from it (16
+// requests of 10k-32k tokens, rank 16: 262 us either way).
+bool decode_balances(int64_t s_cap, int batch, int n_tok, int head_dim, int rank, int n_splits, bool shared_base, bool staged) {
+  return dec_vdma(head_dim, rank, staged) && batch > 1 && batch <= 64 && n_tok == 1 && !shared_base && n_splits >= 2 &&
+         2 * n_splits <= kMaxSplits && s_cap / n_splits >= 8 * TK;
+}
+
+bool decode_direct_paged(int n_tok, int max_blk) { return n_tok == 1 && max_blk <= kLdsBlocks; }
+
+void decode_plan(int64_t s_cap, int batch, int n_kv, int group, int head_dim, int rank, bool shared_base, bool staged,
                  int cus, int* n_splits) {
   const int64_t tiles = (s_cap + TK - 1) / TK;
   const int nw = shared_base ? SH_W : dec_waves(rank);
@@ -1306,7 +1443,7 @@ void decode_plan(int64_t s_cap, int batch, int n_kv, int group, int head_dim, in
   // combine cost as much as many sub-blocks (see its comment).
   int64_t ns, st;
   plan(2, &ns, &st);
-  if (st < 8 || shared_base || dec_vdma(head_dim, rank, paged)) plan(1, &ns, &st);
+  if (st < 8 || shared_base || dec_vdma(head_dim, rank, staged)) plan(1, &ns, &st);
   *n_splits = (int)ns;
 }
 
