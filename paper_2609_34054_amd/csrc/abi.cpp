@@ -449,7 +449,7 @@ namespace {
 // Partials of a chunk that runs as a decode (0: it does not).
 size_t chunk_decode_bytes(const lrsa_dims* dims, int rank, int cus, int* n_splits) {
   const int group = dims->n_q_heads / dims->n_kv_heads;
-  if (!prc::decode_takes_chunk(dims->n_tok, group)) return 0;
+  if (!prc::decode_takes_chunk(dims->s_cap, dims->n_tok, group)) return 0;
   prc::decode_plan(dims->s_cap, dims->batch, dims->n_kv_heads, group, dims->head_dim, rank, false, true, cus, n_splits);
   return prc::decode_workspace_bytes(dims->batch * dims->n_tok, dims->n_q_heads, *n_splits, dims->head_dim, rank);
 }
@@ -469,7 +469,7 @@ size_t workspace_size(const lrsa_dims* dims, bool paged, bool optional = true) {
     // brings L_k).
     int splits = 1;
     const int group = dims->n_q_heads / dims->n_kv_heads;
-    prc::prefill_plan(dims->n_tok, group, dims->n_kv_heads, dims->batch, dims->s_cap, plan_cus(), &splits);
+    prc::prefill_plan(dims->n_tok, group, dims->n_kv_heads, dims->batch, dims->s_cap, plan_cus(), &splits, nullptr);
     const size_t parts =
         prc::prefill_workspace_bytes(dims->batch, dims->n_tok, dims->n_q_heads, splits, dims->head_dim, r);
     if (optional) {
@@ -484,9 +484,10 @@ size_t workspace_size(const lrsa_dims* dims, bool paged, bool optional = true) {
     return parts;
   }
   int n_splits = 0;
-  // Paged caches always take the per-request decode kernel; the size covers
-  // either of its forms (the register-staged one has at least as many splits).
-  const bool shared = !paged && prc::decode_shares_base(dims->batch, dims->kv_req_stride);
+  // Paged caches always take the per-request decode kernel (requests may share
+  // some blocks and not others); the size covers either of its forms (the
+  // register-staged one has at least as many splits).
+  const bool shared = !paged && prc::decode_shares_base(dims->s_cap, dims->batch, dims->kv_req_stride);
   prc::decode_plan(dims->s_cap, dims->batch, dims->n_kv_heads, dims->n_q_heads / dims->n_kv_heads, dims->head_dim, r,
                    shared, paged, plan_cus(), &n_splits);
   if (optional) {
@@ -497,6 +498,13 @@ size_t workspace_size(const lrsa_dims* dims, bool paged, bool optional = true) {
                      shared, false, plan_cus(), &ns);
     if (prc::decode_balances(dims->s_cap, dims->batch, dims->n_tok, dims->head_dim, r, ns, shared, false) && 2 * ns > n_splits)
       n_splits = 2 * ns;
+  } else if (!paged && !shared && prc::decode_can_share_base(dims->batch, dims->kv_req_stride)) {
+    // A short shared base takes the shared kernel after all where only its
+    // partials fit.
+    int ns = 0;
+    prc::decode_plan(dims->s_cap, dims->batch, dims->n_kv_heads, dims->n_q_heads / dims->n_kv_heads, dims->head_dim, r,
+                     true, false, plan_cus(), &ns);
+    if (ns < n_splits) n_splits = ns;
   }
   return prc::decode_workspace_bytes(dims->batch, dims->n_q_heads, n_splits, dims->head_dim, r);
 }
@@ -530,12 +538,17 @@ prc_status attention_impl(const char* who, const lrsa_dims* dims, const lrsa_pag
 #if PRC_DEVICE_CHECKS
     if (prc_status dc = device_data_check(who, positions, kv_len, a.batch, a.n_tok, a.s_cap, st)) return dc;
 #endif
-    prc::decode_plan(a.s_cap, a.batch, a.n_kv, a.group, a.head_dim, a.rank,
-                     pg == nullptr && prc::decode_shares_base(a.batch, a.kv_stride),
-                     pg != nullptr && !prc::decode_direct_paged(a.n_tok, a.max_blk), cus, &a.n_splits);
+    bool shared = pg == nullptr && prc::decode_shares_base(a.s_cap, a.batch, a.kv_stride);
+    a.dec_direct = pg != nullptr && prc::decode_direct_paged(a.s_cap, a.batch, a.n_tok, a.n_kv, a.head_dim, a.rank, a.max_blk, cus);
+    const bool staged = pg != nullptr && !a.dec_direct;
+    prc::decode_plan(a.s_cap, a.batch, a.n_kv, a.group, a.head_dim, a.rank, shared, staged, cus, &a.n_splits);
+    if (pg == nullptr && !shared && prc::decode_can_share_base(a.batch, a.kv_stride) &&
+        workspace_bytes < prc::decode_workspace_bytes(a.batch, a.n_q, a.n_splits, a.head_dim, a.rank)) {
+      shared = true;
+      prc::decode_plan(a.s_cap, a.batch, a.n_kv, a.group, a.head_dim, a.rank, shared, staged, cus, &a.n_splits);
+    }
+    a.dec_shared = shared;
     // With room for twice the partials the splits follow the requests' lengths.
-    const bool shared = pg == nullptr && prc::decode_shares_base(a.batch, a.kv_stride);
-    const bool staged = pg != nullptr && !prc::decode_direct_paged(a.n_tok, a.max_blk);
     if (prc::decode_balances(a.s_cap, a.batch, a.n_tok, a.head_dim, a.rank, a.n_splits, shared, staged) &&
         workspace_bytes >= prc::decode_workspace_bytes(a.batch, a.n_q, 2 * a.n_splits, a.head_dim, a.rank)) {
       a.wg_total = a.n_splits * a.batch;
@@ -559,7 +572,7 @@ prc_status attention_impl(const char* who, const lrsa_dims* dims, const lrsa_pag
     a.ws = static_cast<float*>(workspace);
     return launch_status(prc::launch_decode(a, st), who, " (prefill)");
   }
-  prc::prefill_plan(a.n_tok, a.group, a.n_kv, a.batch, a.s_cap, plan_cu, &a.pf_splits);
+  prc::prefill_plan(a.n_tok, a.group, a.n_kv, a.batch, a.s_cap, plan_cu, &a.pf_splits, &a.pf_min_tiles);
   // Split partials first (required when the plan splits), then the tile
   // cache, taken when the workspace has room for it (a smaller or absent
   // workspace only means every workgroup rebuilds every tile).

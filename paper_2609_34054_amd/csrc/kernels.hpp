@@ -50,11 +50,14 @@ struct AttnArgs {
   int32_t head_dim;
   int32_t rank;
   int32_t n_splits;     // splits with room in the workspace per (request, token, head) row
+  int32_t dec_shared;   // decode: 1 for the shared-base kernel
+  int32_t dec_direct;   // paged decode: 1 for the form that stages V by direct loads
   int32_t wg_total;     // decode: split workgroups of the whole batch when its splits are
                         // balanced over the requests' lengths, else 0
   int32_t dec_group;    // decode: consecutive requests whose splits cover the same
                         // ranges (1: each its own); 0: a prefill, whose splits all write
   int32_t pf_splits;    // prefill: KV splits per row tile (1: none)
+  int32_t pf_min_tiles; // prefill: KV tiles a split takes at least
   // Prefill tile cache in the workspace (tc_data == nullptr: off).  The
   // rebuilt K rows and V^T fragments of a full 64-token tile, in the LDS
   // layout, in eight 4 KB parts (one per wave), [request][KV head][tile][part],
@@ -69,8 +72,10 @@ struct AttnArgs {
 // Decode (one query token per request): split-KV partials + merge.
 int decode_tile_tokens();
 // A decode batch whose requests all read one base cache (request stride 0)
-// runs the shared-base kernel: each base tile is read once for all of them.
-bool decode_shares_base(int batch, int64_t kv_req_stride);
+// can run the shared-base kernel: each base tile is read once for all of them.
+bool decode_can_share_base(int batch, int64_t kv_req_stride);
+// Whether it does, given the workspace of the form it then takes.
+bool decode_shares_base(int64_t s_cap, int batch, int64_t kv_req_stride);
 // `cus`: compute units of the device the call runs on; `staged`: the call
 // takes the form with V staged in registers where the rank has two (paged
 // calls with long block tables, several query tokens).  The
@@ -82,13 +87,13 @@ void decode_plan(int64_t s_cap, int batch, int n_kv, int group, int head_dim, in
 // lengths, over n_splits * batch workgroups, given room for twice as many
 // partials a row.
 bool decode_balances(int64_t s_cap, int batch, int n_tok, int head_dim, int rank, int n_splits, bool shared_base, bool staged);
-// Whether a paged call's block tables (max_blk entries a request) let it take
-// the form that stages V by direct loads.
-bool decode_direct_paged(int n_tok, int max_blk);
+// Whether a paged call takes the form that stages V by direct loads (block
+// tables of max_blk entries a request short enough, splits long enough).
+bool decode_direct_paged(int64_t s_cap, int batch, int n_tok, int n_kv, int head_dim, int rank, int max_blk, int cus);
 // Whether a prefill of this shape runs as a decode with several tokens (given
 // the workspace for its partials: batch * n_tok rows).  It never shares a base
 // between requests, and plans as paged calls do.
-bool decode_takes_chunk(int n_tok, int group);
+bool decode_takes_chunk(int64_t s_cap, int n_tok, int group);
 size_t decode_workspace_bytes(int batch, int n_q, int n_splits, int head_dim, int rank);
 hipError_t launch_decode(const AttnArgs& a, hipStream_t stream);
 
@@ -99,7 +104,7 @@ hipError_t launch_split_merge(const AttnArgs& a, hipStream_t stream);
 // Prefill (several query tokens per request): causal flash attention.  A
 // call with too few (row tile, KV head, request) units to fill the GPU is
 // also split over the KV tiles, each split writing partials for the merge.
-void prefill_plan(int n_tok, int group, int n_kv, int batch, int64_t s_cap, int cus, int* splits);
+void prefill_plan(int n_tok, int group, int n_kv, int batch, int64_t s_cap, int cus, int* splits, int* min_tiles);
 size_t prefill_workspace_bytes(int batch, int n_tok, int n_q, int splits, int head_dim, int rank);
 // Whether a prefill call shares rebuilt tiles through the workspace tile
 // cache: contiguous caches, d = 128, rank >= 16 with LR on the keys, and

@@ -1326,7 +1326,7 @@ hipError_t launch_t(AttnArgs a, hipStream_t st) {
   const auto go = [&](auto paged, auto mt) {
     constexpr bool P = decltype(paged)::value, M = decltype(mt)::value;
     if constexpr (P && !M && dec_vdma(D, R, false)) {
-      if (decode_direct_paged(a.n_tok, a.max_blk)) {
+      if (a.dec_direct) {
         constexpr int nw = dec_nw(D, R, false);
         const dim3 grid(gx, (a.n_kv + nw - 1) / nw, gz);
         hipLaunchKernelGGL((lrsa_decode_kernel<D, R, P, M, false>), grid, dim3(64 * nw), 0, st, a);
@@ -1394,7 +1394,15 @@ hipError_t launch_r(const AttnArgs& a, hipStream_t st, bool shared) {
 
 int decode_tile_tokens() { return TK; }
 
-bool decode_shares_base(int batch, int64_t kv_req_stride) { return batch > 1 && kv_req_stride == 0; }
+// Below 2048 tokens the base tiles stay in the L2 whoever reads them, and the
+// shared-base kernel's longer start costs more than its one read saves (8 / 2 /
+// 16 requests of 300 tokens: 19.3 / 16.5 / 21.4 us shared, 16.6 / 14.9 / 18.4
+// each by itself; of 1200: 19.0 / 14.8 / 25.9 and 17.9 / 13.9 / 25.6; 8 of 2400:
+// 21.9 and 23.0).
+bool decode_can_share_base(int batch, int64_t kv_req_stride) { return batch > 1 && kv_req_stride == 0; }
+bool decode_shares_base(int64_t s_cap, int batch, int64_t kv_req_stride) {
+  return decode_can_share_base(batch, kv_req_stride) && s_cap >= 2048;
+}
 
 // The one-round kernel has nothing left to even out requests of different
 // lengths with, so batches of 2 to 64 of them cut their splits by length (a
@@ -1406,8 +1414,6 @@ bool decode_balances(int64_t s_cap, int batch, int n_tok, int head_dim, int rank
   return dec_vdma(head_dim, rank, staged) && batch > 1 && batch <= 64 && n_tok == 1 && !shared_base && n_splits >= 2 &&
          2 * n_splits <= kMaxSplits && s_cap / n_splits >= 8 * TK;
 }
-
-bool decode_direct_paged(int n_tok, int max_blk) { return n_tok == 1 && max_blk <= kLdsBlocks; }
 
 void decode_plan(int64_t s_cap, int batch, int n_kv, int group, int head_dim, int rank, bool shared_base, bool staged,
                  int cus, int* n_splits) {
@@ -1422,6 +1428,12 @@ void decode_plan(int64_t s_cap, int batch, int n_kv, int group, int head_dim, in
   auto plan = [&](int64_t rounds, int64_t* ns_out, int64_t* st_out) {
     const int64_t target_wgs = rounds * (cus > 0 ? cus : 1) * 8 / nw;
     int64_t ns = (target_wgs + groups - 1) / groups;
+    // Rounded down where splits are long: a split more for each request starts
+    // a few workgroups after all others have (per call, rounded up / down: 14
+    // requests of 31.6k tokens, dim 64, 518 / 504 workgroups: 134 / 109 us; 11
+    // of 45.7k, dim 128: 455 / 370 us; 3 of 30k: 111 / 77 us).  Short splits
+    // lose more by a longer one.
+    if (target_wgs / groups >= 4 && tiles >= 8 * ns) ns = target_wgs / groups;
     if (ns < 1) ns = 1;
     if (ns > kMaxSplits) ns = kMaxSplits;
     if (ns > tiles) ns = tiles > 0 ? tiles : 1;
@@ -1447,12 +1459,30 @@ void decode_plan(int64_t s_cap, int batch, int n_kv, int group, int head_dim, in
   *n_splits = (int)ns;
 }
 
+// A paged rank-64 call takes the direct-V form where the register-staged one
+// would run splits of two tiles or more: at one tile there is nothing for the
+// extra waves to overlap with, and its longer start shows (1 request of 1024 /
+// 2048 tokens: 19.9 / 22.0 us staged, 24.9 / 25.8 direct; 3: 22.4 / 34.2 and
+// 26.1 / 26.8; 8: 35.2 / 41.6 and 28.0 / 33.7; 1 of 8192: 36.1 and 28.9).
+bool decode_direct_paged(int64_t s_cap, int batch, int n_tok, int n_kv, int head_dim, int rank, int max_blk, int cus) {
+  if (!dec_vdma(head_dim, rank, false) || n_tok != 1 || max_blk > kLdsBlocks) return false;
+  const int nw = dec_nw(head_dim, rank, true);
+  const int64_t groups = (int64_t)batch * ((n_kv + nw - 1) / nw);
+  const int64_t ns = ((int64_t)(cus > 0 ? cus : 1) * 8 / nw + groups - 1) / groups;
+  return (s_cap + TK - 1) / TK > (ns < kMaxSplits ? ns : kMaxSplits);
+}
+
 // A chunk of a few query tokens whose (token, head) pairs per KV head fit the
 // decode's 16 columns runs as a decode: split over the keys as far as the chip
 // is wide, where a prefill would give one workgroup per KV head (times at most
 // eight splits) 256 rows to fill with 16.  (16 tokens over 528 keys, 4 heads of
 // dim 64, rank 8: 20.9 us as a prefill, 10.8 us so, 6.4 of them the decode.)
-bool decode_takes_chunk(int n_tok, int group) { return n_tok > 1 && n_tok * group <= 16; }
+// Not below 512 tokens, where a prefill has few tiles to walk and needs no
+// merge (3 tokens, group 4, rank 32, over 128 / 256 / 512 / 1024 keys: 12.6 /
+// 16.4 / 23.9 / 27.6 us as a prefill, 17.5 / 18.9 / 21.3 / 17.5 us so).
+bool decode_takes_chunk(int64_t s_cap, int n_tok, int group) {
+  return n_tok > 1 && n_tok * group <= 16 && s_cap >= 512;
+}
 
 size_t decode_workspace_bytes(int batch, int n_q, int n_splits, int head_dim, int rank) {
   return (size_t)batch * n_q * n_splits * (4 + head_dim + rank) * sizeof(float);
@@ -1465,11 +1495,8 @@ hipError_t launch_split_merge(const AttnArgs& a, hipStream_t st) {
 }
 
 hipError_t launch_decode(const AttnArgs& a, hipStream_t st) {
-  // Paged caches go through the per-request kernel (requests may share some
-  // blocks and not others).
-  const bool shared = a.kv_tbl == nullptr && a.n_tok == 1 && decode_shares_base(a.batch, a.kv_stride);
-  if (a.head_dim == 64) return launch_r<64>(a, st, shared);
-  if (a.head_dim == 128) return launch_r<128>(a, st, shared);
+  if (a.head_dim == 64) return launch_r<64>(a, st, a.dec_shared);
+  if (a.head_dim == 128) return launch_r<128>(a, st, a.dec_shared);
   return hipErrorInvalidValue;
 }
 

@@ -271,7 +271,8 @@ lrsa_prefill_kernel(const AttnArgs a) {
   // 65920 tokens, rank 16, 4 splits: 266 -> 111 us).
   int t_lo = 0, t_hi = n_tiles;
   if (nsp > 1) {
-    const int kv_tiles = (int)((kvl + TKV - 1) / TKV), st = (kv_tiles + nsp - 1) / nsp;
+    const int kv_tiles = (int)((kvl + TKV - 1) / TKV), even = (kv_tiles + nsp - 1) / nsp;
+    const int st = even > a.pf_min_tiles ? even : a.pf_min_tiles;
     t_lo = split * st < n_tiles ? split * st : n_tiles;
     t_hi = t_lo + st < n_tiles ? t_lo + st : n_tiles;
   }
@@ -1121,7 +1122,7 @@ hipError_t launch_r(const AttnArgs& a, hipStream_t st) {
 
 }  // namespace
 
-void prefill_plan(int n_tok, int group, int n_kv, int batch, int64_t s_cap, int cus, int* splits) {
+void prefill_plan(int n_tok, int group, int n_kv, int batch, int64_t s_cap, int cus, int* splits, int* min_tiles) {
   // Units of work without a split: (row tile, KV head, request), one
   // workgroup per CU at a time.  Splitting the KV tiles ns ways gives
   // units * ns workgroups of 1/ns the work, so the time per CU goes as
@@ -1144,9 +1145,15 @@ void prefill_plan(int n_tok, int group, int n_kv, int batch, int64_t s_cap, int 
     }
   }
   *splits = 1;
+  if (min_tiles != nullptr) *min_tiles = 1;
   if (best < 2 || best_cost > 0.9 * one_pass) return;
   const int64_t st = (tiles + best - 1) / best;
   *splits = (int)((tiles + st - 1) / st);
+  // With more units than CUs a split only evens out the last round, and its
+  // partials cost as much as many tiles: short contexts in a large cache then
+  // take fewer of the planned splits (3 requests, 1554 queries over 1777 of
+  // 7108 tokens, rank 8, planned 5 ways: 835 us in fifths, 630 so).
+  if (min_tiles != nullptr && units > n_cu) *min_tiles = (int)(st < 32 ? st : 32);
 }
 
 size_t prefill_workspace_bytes(int batch, int n_tok, int n_q, int splits, int head_dim, int rank) {

@@ -23,12 +23,15 @@ CASES = [
     ("decode_shared_r64", 128, 64, 8, 2, 1, [500, 499, 100, 1, 64], 4096, "kv", "shared"),
     # Shared base: 4, 3 and 2 requests per 16 columns, one and two groups per
     # workgroup, request slots and columns left over.
-    ("decode_shared_g5_r64", 128, 64, 10, 2, 1, [200, 17, 16, 15, 1, 199, 64], 512, "kv", "shared"),
-    ("decode_shared_g8_r16", 128, 16, 16, 2, 1, [300, 31, 33, 299, 16], 1024, "kv", "shared"),
-    ("decode_shared_g1_d64_r8", 64, 8, 2, 2, 1, [130, 129, 1, 16, 15, 64, 65, 100, 128], 256, "kv", "shared"),
-    ("decode_shared_g3_qv_r32", 128, 32, 6, 2, 1, [500, 480, 17], 600, "v", "shared"),
+    ("decode_shared_g5_r64", 128, 64, 10, 2, 1, [200, 17, 16, 15, 1, 199, 64], 2048, "kv", "shared"),
+    ("decode_shared_g8_r16", 128, 16, 16, 2, 1, [300, 31, 33, 299, 16], 2080, "kv", "shared"),
+    ("decode_shared_g1_d64_r8", 64, 8, 2, 2, 1, [130, 129, 1, 16, 15, 64, 65, 100, 128], 2049, "kv", "shared"),
+    ("decode_shared_short", 128, 16, 8, 2, 1, [130, 129, 1, 33], 2047, "kv", "shared"),  # each request by itself
+    ("decode_shared_g3_qv_r32", 128, 32, 6, 2, 1, [500, 480, 17], 2500, "v", "shared"),
     ("prefill_split", 128, 16, 8, 2, 40, [300, 64, 65], 8192, "kv", "own"),
     ("prefill_split_r8", 128, 8, 8, 2, 16, [1040], 16384, "kv", "own"),
+    # More units than CUs and a cache four times the keys: fewer splits than planned.
+    ("prefill_split_many_units", 64, 8, 64, 16, 1100, [1300], 5200, "kv", "own"),
     ("prefill_split_paged", 128, 32, 8, 2, 20, [129, 700], 8192, "kv", "paged"),
 ]
 

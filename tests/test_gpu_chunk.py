@@ -16,13 +16,14 @@ pytestmark = pytest.mark.gpu
 # id, d, r, n_q, n_kv, n_tok, kv_lens, s_cap, lr ("kv"|"v"|"k"|"none"), positions ("end"|"mid"|"mixed")
 CASES = [
     ("g1_16_tokens", 64, 8, 4, 4, 16, [528], 576, "kv", "end"),
-    ("g4_4_tokens", 128, 16, 8, 2, 4, [300, 64, 5], 320, "kv", "end"),
+    ("g4_4_tokens", 128, 16, 8, 2, 4, [300, 64, 5], 512, "kv", "end"),
     ("g4_3_tokens_long", 128, 16, 32, 8, 3, [5000], 8192, "kv", "end"),
-    ("g8_2_tokens", 128, 32, 16, 2, 2, [333, 34, 2], 384, "kv", "mid"),
+    ("g8_2_tokens", 128, 32, 16, 2, 2, [333, 34, 2], 576, "kv", "mid"),
     ("g5_3_tokens_r64", 128, 64, 10, 2, 3, [700, 65], 704, "kv", "end"),
-    ("g3_5_tokens_mixed", 128, 16, 6, 2, 5, [200, 129], 256, "kv", "mixed"),
-    ("g2_7_tokens_qv", 64, 32, 4, 2, 7, [97], 128, "v", "end"),
-    ("g1_9_tokens_k_only", 64, 8, 9, 9, 9, [130], 192, "k", "end"),
+    ("g3_5_tokens_mixed", 128, 16, 6, 2, 5, [200, 129], 512, "kv", "mixed"),
+    ("g2_7_tokens_qv", 64, 32, 4, 2, 7, [97], 640, "v", "end"),
+    ("g1_9_tokens_k_only", 64, 8, 9, 9, 9, [130], 512, "k", "end"),
+    ("g4_4_tokens_below", 128, 16, 8, 2, 4, [300, 5], 448, "kv", "end"),  # short caches stay a prefill
     ("g4_2_tokens_plain", 128, 16, 8, 2, 2, [2000, 31], 2048, "none", "end"),
 ]
 
@@ -67,7 +68,7 @@ def test_chunk_as_decode(case):
 
 def test_chunk_without_workspace_is_still_taken():
     cfg = mk_cfg(91, 8, 2, 128, 16)
-    c = attention_case(cfg, batch=2, n_tok=3, kv_len=[300, 64], positions=[[297, 298, 299], [61, 62, 63]], s_cap=320)
+    c = attention_case(cfg, batch=2, n_tok=3, kv_len=[300, 64], positions=[[297, 298, 299], [61, 62, 63]], s_cap=576)
     g = to_dev(c)
     dims = prc.make_dims(g["Q"], g["K_base"], g["L_k"], g["L_v"], g["B_k"], g["B_v"], cfg.theta)
     assert prc.workspace_size(dims) > 0
