@@ -230,9 +230,14 @@ typedef struct lrsa_dims {
  *              unevenly that splitting the KV tiles 2-8 ways shortens the
  *              modelled time (rounds of one unit per CU) by at least 10%.
  *              For a chunk of at most 16 (token, head) pairs per KV head
- *              (n_tok * n_q / n_kv <= 16) the size covers partials that let it
- *              run as a decode, split over the keys; given less, or NULL, it
- *              runs as any other prefill.
+ *              (n_tok * n_q / n_kv <= 16) over at least 512 tokens of capacity
+ *              the size covers partials that let it run as a decode, split
+ *              over the keys; given less, or NULL, it runs as any other prefill.
+ *              For a rank-64 decode of several requests (d = 128) the size has
+ *              room for splits balanced over their lengths, and for requests
+ *              that share a base of under 2048 tokens for each to run by
+ *              itself; such calls are also taken with less, down to the
+ *              partials of even splits, or of the shared form.
  *              For a prefill of rank 8, 16, 32 or 64 with at least 8 row
  *              tiles (256 query rows each) per KV head, d = 128 and
  *              contiguous caches, the size also covers an optional tile
