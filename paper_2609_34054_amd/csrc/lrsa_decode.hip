@@ -873,6 +873,10 @@ lrsa_decode_shared_kernel(const AttnArgs a, int n_grp) {
   // L_v tiles: one per request up to rank 16, so that all are written with V
   // at the head of a sub-block; above, one that the requests use in turn.
   constexpr int NLT = R <= 16 ? RPB : 1, LVT = 16 * C::LV_ROW;
+  // P L_v of every column with each request's L_v, of which a column keeps its
+  // own request's: an accumulator per request up to rank 32, selected at the
+  // end; above, one, selected at every sub-block (the registers end there).
+  constexpr int NLA = C::RC <= 2 ? RPB : 1;
   constexpr int kV = SH_W * 16 * C::V_ROW * 2, kLv = SH_W * NLT * LVT * 2;
   constexpr int kOff = SB * C::CS_ROW * 8 + (SB * C::CS_ROW % 2) * 8, kBase = SH_W * 2 * C::HALF * 8;
   constexpr int kLoop = kBk + kV + kLv + kOff + kBase;
@@ -1023,11 +1027,13 @@ lrsa_decode_shared_kernel(const AttnArgs a, int n_grp) {
   for (int i = lane; i < NLT * LVT; i += 64) lvl[i] = 0;
 
   float m_run = -INFINITY, l_part = 0.f;
-  f32x4 acc[C::NBLK], accl[C::RC];
+  f32x4 acc[C::NBLK], accl[NLA][C::RC];
 #pragma unroll
   for (int blk = 0; blk < C::NBLK; ++blk) acc[blk] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int rc = 0; rc < C::RC; ++rc) accl[rc] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int r = 0; r < NLA; ++r)
+#pragma unroll
+    for (int rc = 0; rc < C::RC; ++rc) accl[r][rc] = f32x4{0.f, 0.f, 0.f, 0.f};
   const int tr_row = 4 * q + (c16 >> 2), tr_col = 4 * (c16 & 3);
 
   // Exact angles of a sub-block's first token, a sub-block ahead.
@@ -1142,7 +1148,9 @@ lrsa_decode_shared_kernel(const AttnArgs a, int n_grp) {
 #pragma unroll
       for (int blk = 0; blk < C::NBLK; ++blk) acc[blk] *= alpha;
 #pragma unroll
-      for (int rc = 0; rc < C::RC; ++rc) accl[rc] *= alpha;
+      for (int r = 0; r < NLA; ++r)
+#pragma unroll
+        for (int rc = 0; rc < C::RC; ++rc) accl[r][rc] *= alpha;
       l_part *= alpha;
       m_run = mn;
     }
@@ -1155,20 +1163,31 @@ lrsa_decode_shared_kernel(const AttnArgs a, int n_grp) {
     const i16x4 pb = as_i16x4(pw);
     __builtin_amdgcn_wave_barrier();
     // ---- O^T += V^T P^T; (P L_v)^T += L_v^T P^T, each request its columns ------
+    // A weight of zero does not keep an infinity or a NaN out (0 x Inf is NaN),
+    // so the other requests' L_v are kept out of a column by selection.
 #pragma unroll
     for (int blk = 0; blk < C::NBLK; ++blk)
       acc[blk] = mfma16x16x16(lds_read_tr(vl + tr_row * C::V_ROW + blk * 16 + tr_col), pb, acc[blk]);
     if (has_lv) {
+      f32x4 own[C::RC];
 #pragma unroll
       for (int r = 0; r < RPB; ++r) {
         if constexpr (NLT == 1) lv_store(r);
         __builtin_amdgcn_wave_barrier();
-        const i16x4 pr = as_i16x4(slot == r ? pw : u32x2{0u, 0u});
 #pragma unroll
-        for (int rc = 0; rc < C::RC; ++rc)
-          accl[rc] = mfma16x16x16(lds_read_tr(lvl + (r % NLT) * LVT + tr_row * C::LV_ROW + rc * 16 + tr_col), pr, accl[rc]);
+        for (int rc = 0; rc < C::RC; ++rc) {
+          f32x4& acl = accl[r % NLA][rc];
+          const f32x4 x = mfma16x16x16(lds_read_tr(lvl + (r % NLT) * LVT + tr_row * C::LV_ROW + rc * 16 + tr_col), pb, acl);
+          if constexpr (NLA == RPB) acl = x;
+          else
+#pragma unroll
+            for (int i = 0; i < 4; ++i) own[rc][i] = r == 0 || slot == r ? x[i] : own[rc][i];
+        }
         __builtin_amdgcn_wave_barrier();
       }
+      if constexpr (NLA == 1)
+#pragma unroll
+        for (int rc = 0; rc < C::RC; ++rc) accl[0][rc] = own[rc];
     }
     if constexpr (NLT == 1) {
       load_lv(tn);
@@ -1186,8 +1205,14 @@ lrsa_decode_shared_kernel(const AttnArgs a, int n_grp) {
 #pragma unroll
     for (int blk = 0; blk < C::NBLK; ++blk) *reinterpret_cast<f32x4*>(pr + blk * 16 + q * 4) = acc[blk];
 #pragma unroll
-    for (int rc = 0; rc < C::RC; ++rc)
-      if (rc * 16 + q * 4 < R) *reinterpret_cast<f32x4*>(pr + D + rc * 16 + q * 4) = accl[rc];
+    for (int rc = 0; rc < C::RC; ++rc) {
+      f32x4 own = accl[0][rc];
+#pragma unroll
+      for (int r = 1; r < NLA; ++r)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) own[i] = slot == r ? accl[r][rc][i] : own[i];
+      if (rc * 16 + q * 4 < R) *reinterpret_cast<f32x4*>(pr + D + rc * 16 + q * 4) = own;
+    }
     if (q == 0) {
       pr[D + R] = m_run;
       pr[D + R + 1] = l_part;
