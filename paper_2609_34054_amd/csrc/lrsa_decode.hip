@@ -905,6 +905,10 @@ lrsa_decode_shared_kernel(const AttnArgs a, int n_grp) {
   int t_end_r[RPB];  // per request of this wave (uniform)
 #pragma unroll
   for (int i = 0; i < RPB; ++i) t_end_r[i] = clip(__builtin_amdgcn_readlane(vis_lane, grp * RPB + i));
+  int t_end_min = t_end_wg;  // up to here every request of this wave has keys
+#pragma unroll
+  for (int i = 0; i < RPB; ++i) t_end_min = b0 + i < a.batch ? min(t_end_min, t_end_r[i]) : t_end_min;
+  t_end_min = __builtin_amdgcn_readfirstlane(t_end_min);
   // This lane's column: request slot, head, end.
   const int slot = c16 / G, b_l = b0 + slot;
   const bool col_ok = slot < RPB && b_l < a.batch;
@@ -1164,10 +1168,20 @@ lrsa_decode_shared_kernel(const AttnArgs a, int n_grp) {
     __builtin_amdgcn_wave_barrier();
     // ---- O^T += V^T P^T; (P L_v)^T += L_v^T P^T, each request its columns ------
     // A weight of zero does not keep an infinity or a NaN out (0 x Inf is NaN),
-    // so the other requests' L_v are kept out of a column by selection.
+    // so rows that are not a column's own are kept out by selection: base rows
+    // past a shorter request's end here, every other request's L_v below.
+    if (ts < t_end_min) {
 #pragma unroll
-    for (int blk = 0; blk < C::NBLK; ++blk)
-      acc[blk] = mfma16x16x16(lds_read_tr(vl + tr_row * C::V_ROW + blk * 16 + tr_col), pb, acc[blk]);
+      for (int blk = 0; blk < C::NBLK; ++blk)
+        acc[blk] = mfma16x16x16(lds_read_tr(vl + tr_row * C::V_ROW + blk * 16 + tr_col), pb, acc[blk]);
+    } else {
+#pragma unroll
+      for (int blk = 0; blk < C::NBLK; ++blk) {
+        const f32x4 x = mfma16x16x16(lds_read_tr(vl + tr_row * C::V_ROW + blk * 16 + tr_col), pb, acc[blk]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[blk][i] = n_vis > 0 ? x[i] : acc[blk][i];
+      }
+    }
     if (has_lv) {
       f32x4 own[C::RC];
 #pragma unroll

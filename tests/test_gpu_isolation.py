@@ -53,3 +53,19 @@ def test_one_agents_rows_stay_its_own(case, name):
         rest = [b for b in range(O.shape[0]) if b != bad]
         assert not torch.isfinite(Op[bad].float()).all()
         assert torch.equal(Op[rest], O[rest]) and torch.equal(lp[rest], lse[rest])
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: f"d{c[0]}r{c[1]}g{c[2] // c[3]}")
+def test_base_rows_of_the_longest_request_alone(case):
+    """Base rows that only the longest request sees (a 16-token sub-block and
+    more past the others' ends)."""
+    print(f"isolation base {case}", flush=True)
+    cfg, g = _case(case)
+    O, lse = _run(cfg, g)
+    end = case[4][0]
+    p = dict(g, V_base=g["V_base"].clone())
+    p["V_base"][0, end - 10:end - 5] = float("inf")
+    p["V_base"][0, end - 5] = float("nan")
+    Op, lp = _run(cfg, p)
+    assert not torch.isfinite(Op[0].float()).all()
+    assert torch.equal(Op[1:], O[1:]) and torch.equal(lp[1:], lse[1:])
