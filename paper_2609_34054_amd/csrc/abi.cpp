@@ -302,7 +302,8 @@ PRC_API prc_status precompute_lr_cache(const uint16_t* X, int64_t T, int64_t d_i
   if (d_in < 1 || d_in % 8) return fail(PRC_EUNSUPPORTED, "d_in=%lld must be a positive multiple of 8", (long long)d_in);
   if (ld_x < d_in) return fail(PRC_ESHAPE, "ld_x=%lld < d_in=%lld", (long long)ld_x, (long long)d_in);
   if (ld_x % 8) return fail(PRC_EALIGN, "ld_x=%lld is not a multiple of 8 elements", (long long)ld_x);
-  // Tiles of up to 128 rows are addressed with 32-bit byte offsets.
+  // Tiles of up to 128 rows are addressed with 31-bit byte offsets (the launch
+  // keeps its larger tiles to row strides below 2^22).
   if (ld_x >= (1LL << 23)) return fail(PRC_EUNSUPPORTED, "ld_x=%lld must be below 2^23", (long long)ld_x);
   if (n_proj < 1 || n_agents < 1) return fail(PRC_EINVAL, "n_proj=%d, n_agents=%d must be positive", n_proj, n_agents);
   if (!rank_ok(rank)) return fail(PRC_EUNSUPPORTED, "rank=%d (built: 8, 16, 32, 64)", rank);

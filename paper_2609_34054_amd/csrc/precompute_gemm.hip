@@ -900,16 +900,18 @@ hipError_t launch_precompute(const PrecomputeArgs& a, hipStream_t st) {
   // smaller tile wins (1000 tokens x 2304 columns: 57, 35, 48, 56, 65 us in
   // this order), over full ones the larger (4096 x 2304: 188, 107, 93, 97, 71
   // us; 2048 x 2816, d_in 5120: 148, 86, 67, 60, 71 us).  128-wide tiles need
-  // the K/V boundary on a tile edge.
+  // the K/V boundary on a tile edge; 256-token tiles need their rows of X within
+  // the 31 bits of their byte offsets (INT32_MIN, past them, marks what is not read).
+  const bool wide_ok = a.ld_x * 2 * WD_TT <= (1LL << 31) - 2;
   int n_wt, n_ct;
   const double kd = (double)a.d_in / 4096.0;
   const auto model = [&](double fixed, double per_k, int64_t tiles) { return (fixed + per_k * kd) * (double)cdiv(tiles, cus); };
   const double t[5] = {
       model(2.7, 15.8, (2 * a.nkv / 64 + cdiv(a.n_cols, 64)) * cdiv(a.T, 64)),
       a.nkv % 128 == 0 ? model(5.0, 31.0, (2 * a.nkv / 128 + cdiv(a.n_cols, 128)) * cdiv(a.T, 128)) : 1e30,
-      model(5.0, 45.0, wide_tiles<6>(a, &n_wt, &n_ct)),
-      model(6.6, 42.4, wide_tiles<8>(a, &n_wt, &n_ct)),
-      model(8.4, 49.6, wide_tiles<10>(a, &n_wt, &n_ct)),
+      wide_ok ? model(5.0, 45.0, wide_tiles<6>(a, &n_wt, &n_ct)) : 1e30,
+      wide_ok ? model(6.6, 42.4, wide_tiles<8>(a, &n_wt, &n_ct)) : 1e30,
+      wide_ok ? model(8.4, 49.6, wide_tiles<10>(a, &n_wt, &n_ct)) : 1e30,
   };
   int best = 0;
   for (int i = 1; i < 5; ++i)

@@ -86,3 +86,27 @@ def test_gemm_edges(case):
         assert np.max(np.abs(mine - ref) - 2 ** -7 * np.abs(ref)) <= 2e-2, name
         rest = np.delete(got, at, axis=axis)
         assert (rest == sentinel).all(), name  # rows outside the segment are untouched
+
+
+@pytest.mark.parametrize("ld_x", [2 ** 22 - 8, 2 ** 22, 2 ** 23 - 8])
+def test_rows_far_apart(ld_x):
+    """Row strides at the edge of the 256-token tiles' byte offsets and at the
+    largest accepted one, with a tail of k; whatever lies between the rows is NaN."""
+    T, d_in, n_kv, d, n_proj, N, r = 300, 72, 1, 64, 2, 64, 64
+    print(f"gemm ld_x {ld_x}", flush=True)
+    X = normal_bf16((T, d_in), 1.0, 7901)
+    W = normal_bf16((d_in, 2 * n_kv * d), 1.0 / math.sqrt(d_in), 7902)
+    A = normal_bf16((d_in, n_proj * N * r), 1.0 / math.sqrt(d_in), 7903)
+    room = torch.full(((T - 1) * ld_x + d_in,), float("nan"), dtype=torch.bfloat16, device="cuda")
+    Xs = room.as_strided((T, d_in), (ld_x, 1))
+    Xs.copy_(X)
+    z = lambda *shape: torch.zeros(shape, dtype=torch.bfloat16, device="cuda")  # noqa: E731
+    K, V, L = prc.project_kv_and_lr_cache(Xs, W.cuda(), A.cuda(), n_kv, d, n_proj, N, r, z(T, n_kv, d), z(T, n_kv, d),
+                                          z(n_proj, N, T, r), rope_theta=1e4)
+    torch.cuda.synchronize()
+    Wn = f64(W)
+    Kr, Vr, Lr = oracle.project_kv_and_lr(f64(X), Wn[:, :n_kv * d], Wn[:, n_kv * d:], f64(A), n_kv, n_proj, N, r,
+                                          np.arange(T), 1e4)
+    for name, got, ref in (("K", K, Kr), ("V", V, Vr), ("L", L, Lr)):
+        got = f64(got)
+        assert np.isfinite(got).all() and np.linalg.norm(got - ref) / np.linalg.norm(ref) <= PRE_REL, name
