@@ -399,8 +399,7 @@ template <int NB>
 __global__ void __launch_bounds__((4 + WD_NL) * 64, 2) project_wide_kernel(const PrecomputeArgs a, int n_wt, int n_ct, int n_tt) {
   using C = Wide<NB>;
   __shared__ __attribute__((aligned(1024))) char ring[WD_NST * C::SB];
-  __shared__ double w2pi_lds[kMaxHalfDim];    // the epilogue's RoPE frequencies,
-  __shared__ float2 rot16_lds[kMaxHalfDim];   // and their rotation by 16 positions
+  __shared__ double w2pi_lds[kMaxHalfDim];  // the epilogue's RoPE frequencies
   const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   // Each XCD takes a contiguous eighth of the tiles, column tiles fastest.
   const int n_tiles = n_ct * n_tt, per = (n_tiles + NXCD - 1) / NXCD;
@@ -482,13 +481,7 @@ __global__ void __launch_bounds__((4 + WD_NL) * 64, 2) project_wide_kernel(const
     return;
   }
 
-  if (!lr && tid < half) {
-    const double wj = a.w2pi[tid];
-    float c, sn;
-    rope_cs(16, wj, c, sn);
-    w2pi_lds[tid] = wj;
-    rot16_lds[tid] = make_float2(c, sn);
-  }
+  if (!lr && tid < half) w2pi_lds[tid] = a.w2pi[tid];
   // ---- compute waves -------------------------------------------------------------
   const int q = lane >> 4, c16 = lane & 15, wr = wv >> 1, wc = wv & 1;
   f32x4 acc[C::UW][8];
@@ -575,31 +568,37 @@ __global__ void __launch_bounds__((4 + WD_NL) * 64, 2) project_wide_kernel(const
       const int pos0 = (int)(a.tok_offset + tok0) + 128 * wr + c16;
       uint16_t* kp = a.Kout + hd * a.head_dim + j0 + (q >= 2 ? half : 0);
       double wj[4];
-      float cd[4], sd[4], cs[4], sn[4];  // rotation by 16 positions; angle of token block m
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        wj[i] = w2pi_lds[j0 + i];
-        cd[i] = rot16_lds[j0 + i].x;
-        sd[i] = rot16_lds[j0 + i].y;
-      }
+      for (int i = 0; i < 4; ++i) wj[i] = w2pi_lds[j0 + i];
 #pragma unroll
-      for (int m = 0; m < 8; ++m) {
-        float o[4];
+      for (int m = 0; m < 8; m += 2) {
+        // Lanes l and l ^ 32 need the same angles, each reduced in fp64: one
+        // forms those of token block m, the other those of m + 1, and they swap.
+        float cs[2][4], sn[2][4], o[2][4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          if (m % 4 == 0) {
-            rope_cs(pos0 + 16 * m, wj[i], cs[i], sn[i]);
-          } else {
-            const float c = cs[i] * cd[i] - sn[i] * sd[i];
-            sn[i] = sn[i] * cd[i] + cs[i] * sd[i];
-            cs[i] = c;
+          float c, sw;
+          rope_cs(pos0 + 16 * m + (q < 2 ? 0 : 16), wj[i], c, sw);
+          const auto rc = __builtin_amdgcn_permlane32_swap(__float_as_uint(c), __float_as_uint(c), false, false);
+          const auto rs = __builtin_amdgcn_permlane32_swap(__float_as_uint(sw), __float_as_uint(sw), false, false);
+#pragma unroll
+          for (int e = 0; e < 2; ++e) {
+            cs[e][i] = __uint_as_float(rc[e]);
+            sn[e][i] = __uint_as_float(rs[e]);
           }
-          const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc[u][m][i]), __float_as_uint(acc[u][m][i]), false, false);
-          const float x = __uint_as_float(r[0]), y = __uint_as_float(r[1]);  // lanes l % 32 and l % 32 + 32
-          o[i] = q < 2 ? x * cs[i] - y * sn[i] : y * cs[i] + x * sn[i];
         }
-        if (128 * wr + 16 * m + c16 < toks)
-          *reinterpret_cast<u32x2*>(kp + rowm[m] * a.nkv) = u32x2{pack_bf16(o[0], o[1]), pack_bf16(o[2], o[3])};
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const uint32_t v = __float_as_uint(acc[u][m + e][i]);
+            const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+            const float x = __uint_as_float(r[0]), y = __uint_as_float(r[1]);  // lanes l % 32 and l % 32 + 32
+            o[e][i] = q < 2 ? x * cs[e][i] - y * sn[e][i] : y * cs[e][i] + x * sn[e][i];
+          }
+          if (128 * wr + 16 * (m + e) + c16 < toks)
+            *reinterpret_cast<u32x2*>(kp + rowm[m + e] * a.nkv) = u32x2{pack_bf16(o[e][0], o[e][1]), pack_bf16(o[e][2], o[e][3])};
+        }
       }
       continue;
     }

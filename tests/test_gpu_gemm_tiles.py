@@ -110,3 +110,26 @@ def test_rows_far_apart(ld_x):
     for name, got, ref in (("K", K, Kr), ("V", V, Vr), ("L", L, Lr)):
         got = f64(got)
         assert np.isfinite(got).all() and np.linalg.norm(got - ref) / np.linalg.norm(ref) <= PRE_REL, name
+
+
+def test_key_angles_do_not_depend_on_the_tile():
+    """Every token's angle is reduced in fp64 by itself.  Keys with one weight of
+    1 in the lower half of a head and none in the upper are x cos and x sin, one
+    product each: a long call (256-token tiles) and short ones give equal bits."""
+    T, d_in, n_kv, d, N, r, off = 2100, 40, 8, 128, 8, 16, 60000
+    X = normal_bf16((T, d_in), 1.0, 7911).cuda()
+    W = torch.zeros((d_in, 2 * n_kv * d), dtype=torch.bfloat16, device="cuda")
+    for h in range(n_kv):
+        for j in range(d // 2):
+            W[(5 * h + j) % d_in, h * d + j] = 1.0
+    A = normal_bf16((d_in, 2 * N * r), 1.0 / math.sqrt(d_in), 7912).cuda()
+    out = []
+    for step in (T, 300):
+        K = torch.zeros((off + T, n_kv, d), dtype=torch.bfloat16, device="cuda")
+        V, L = torch.zeros_like(K), torch.zeros((2, N, off + T, r), dtype=torch.bfloat16, device="cuda")
+        for t in range(0, T, step):
+            prc.project_kv_and_lr_cache(X[t:t + step], W, A, n_kv, d, 2, N, r, K, V, L, rope_theta=5e5, tok_offset=off + t)
+        out.append(K)
+    torch.cuda.synchronize()
+    assert out[0][off:].any()
+    assert torch.equal(out[0], out[1]), int((out[0] != out[1]).sum())
