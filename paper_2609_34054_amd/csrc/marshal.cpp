@@ -337,11 +337,28 @@ PyObject* project_paged(PyObject*, PyObject* const* a, Py_ssize_t n) {
   return PyLong_FromLong((long)st);
 }
 
+// A tensor can refuse what is asked of it by throwing (a nested one has no
+// sizes or strides), and nothing may throw through a C entry: such a call is
+// left to Python like any other that is not plain.  (The ABI calls themselves
+// throw nothing, so the interpreter lock is held here.)
+template <PyObject* (*F)(PyObject*, PyObject* const*, Py_ssize_t)>
+PyObject* guarded(PyObject* self, PyObject* const* a, Py_ssize_t n) {
+  try {
+    return F(self, a, n);
+  } catch (...) {
+    return none();
+  }
+}
+template <PyObject* (*F)(PyObject*, PyObject* const*, Py_ssize_t)>
+PyMethodDef method(const char* name) {
+  return {name, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(guarded<F>)), METH_FASTCALL, nullptr};
+}
+
 PyMethodDef methods[] = {
-    {"attention", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(attention)), METH_FASTCALL, nullptr},
-    {"paged", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(paged)), METH_FASTCALL, nullptr},
-    {"project", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(project)), METH_FASTCALL, nullptr},
-    {"project_paged", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(project_paged)), METH_FASTCALL, nullptr},
+    method<attention>("attention"),
+    method<paged>("paged"),
+    method<project>("project"),
+    method<project_paged>("project_paged"),
     {nullptr, nullptr, 0, nullptr},
 };
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_marshal", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};

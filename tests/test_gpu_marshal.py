@@ -117,3 +117,28 @@ def test_projection_calls_agree(monkeypatch):
     for call in bad:
         a, b = _both(call, monkeypatch)
         assert isinstance(a, tuple) and a == b, (a, b)
+
+
+def test_nested_tensors_are_refused(monkeypatch):
+    """Tensors without sizes or strides: asking them for either throws."""
+    _, c = _case()
+    g = to_dev(c)
+    nest = lambda t: torch.nested.nested_tensor(list(t.unbind(0)))  # noqa: E731
+    z = torch.zeros((8, 8), dtype=torch.bfloat16, device="cuda")
+    L = torch.zeros((1, 1, 8, 8), dtype=torch.bfloat16, device="cuda")
+    tbl = torch.zeros((2, 2), dtype=torch.int32, device="cuda")
+    pool = torch.zeros((2, 64, 2, 128), dtype=torch.bfloat16, device="cuda")
+
+    def attention(**kw):
+        a = dict(g, **kw)
+        return prc.lr_shared_attention(a["Q"], a["K_base"], a["V_base"], a["L_k"], a["L_v"], a["B_k"], a["B_v"],
+                                       a["positions"], a["kv_len"], rope_theta=1e4)
+    for call in (lambda: attention(Q=nest(g["Q"])), lambda: attention(K_base=nest(g["K_base"])),
+                 lambda: attention(kv_len=nest(g["positions"])),
+                 lambda: prc.lr_shared_attention_paged(nest(g["Q"]), pool, pool, None, None, None, None, g["positions"],
+                                                       g["kv_len"], tbl, rope_theta=1e4),
+                 lambda: prc.precompute_lr_cache(nest(z), z, 1, 1, 8, L),
+                 lambda: prc.project_kv_and_lr_cache_paged(nest(z), z, z, 1, 64, 1, 1, 8, pool, pool, L, tbl[0],
+                                                           rope_theta=1e4)):
+        a, b = _both(call, monkeypatch)
+        assert isinstance(a, tuple) and a == b, (a, b)
