@@ -655,10 +655,10 @@ PRC_API prc_status lr_shared_attention_noalloc(const lrsa_dims* dims, const uint
   if (need > kStaticWsBytes)
     return fail(PRC_EWORKSPACE, "the call needs %zu bytes of split partials, above the %zu-byte static workspace",
                 need, kStaticWsBytes);
+  // A call that needs no partials leaves the array alone, whatever faster form
+  // it could take there: only calls that need it have to be ordered.
   void* ws = nullptr;
-  int chunk_splits = 0;
-  const size_t chunk = chunk_decode_bytes(dims, c.a.rank, plan_cus(), &chunk_splits);
-  const bool use_ws = need > 0 || (chunk > 0 && chunk <= kStaticWsBytes);
+  const bool use_ws = need > 0;
   if (use_ws) {
     int cus = 0;
     if (prc_status ds = device_ready(&cus)) return ds;

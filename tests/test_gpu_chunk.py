@@ -86,3 +86,24 @@ def test_chunk_without_workspace_is_still_taken():
     for out in (O, On):
         mx, mean = attn_errors(out, Oref)
         assert mx <= ATOL_MAX and mean <= ATOL_MEAN, (mx, mean)
+
+
+def test_noalloc_chunk_without_partials_stays_a_prefill():
+    """A chunk whose prefill needs no partials does not touch the static array of
+    the call that allocates nothing (only calls that do have to be ordered): the
+    bits of the call without any workspace, not those of the split decode."""
+    cfg = mk_cfg(92, 8, 2, 128, 16)
+    c = attention_case(cfg, batch=2, n_tok=3, kv_len=[570, 264], positions=[[567, 568, 569], [261, 262, 263]], s_cap=576)
+    g = to_dev(c)
+    dims = prc.make_dims(g["Q"], g["K_base"], g["L_k"], g["L_v"], g["B_k"], g["B_v"], cfg.theta)
+    O, On = torch.empty_like(g["Q"]), torch.empty_like(g["Q"])
+    p = lambda t: ctypes.c_void_p(t.data_ptr())  # noqa: E731
+    st = prc.lib().lr_shared_attention(ctypes.byref(dims), p(g["Q"]), p(g["K_base"]), p(g["V_base"]), p(g["L_k"]),
+                                       p(g["L_v"]), p(g["B_k"]), p(g["B_v"]), p(g["positions"]), p(g["kv_len"]), p(O),
+                                       None, None, 0, ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert st == 0  # no partials needed
+    prc.lr_shared_attention_noalloc(g["Q"], g["K_base"], g["V_base"], g["L_k"], g["L_v"], g["B_k"], g["B_v"],
+                                    g["positions"], g["kv_len"], rope_theta=cfg.theta, O=On)
+    Od, _ = gpu_attention(g, cfg.theta)
+    torch.cuda.synchronize()
+    assert torch.equal(O, On) and not torch.equal(O, Od)
