@@ -451,7 +451,7 @@ namespace {
 size_t chunk_decode_bytes(const lrsa_dims* dims, int rank, int cus, int* n_splits) {
   const int group = dims->n_q_heads / dims->n_kv_heads;
   if (!prc::decode_takes_chunk(dims->s_cap, dims->n_tok, group)) return 0;
-  prc::decode_plan(dims->s_cap, dims->batch, dims->n_kv_heads, group, dims->head_dim, rank, false, true, cus, n_splits);
+  prc::decode_chunk_plan(dims->s_cap, dims->batch, dims->n_kv_heads, group, dims->head_dim, rank, cus, n_splits);
   return prc::decode_workspace_bytes(dims->batch * dims->n_tok, dims->n_q_heads, *n_splits, dims->head_dim, rank);
 }
 

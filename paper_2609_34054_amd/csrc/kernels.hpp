@@ -83,6 +83,8 @@ bool decode_shares_base(int64_t s_cap, int batch, int64_t kv_req_stride);
 // into at most that many.
 void decode_plan(int64_t s_cap, int batch, int n_kv, int group, int head_dim, int rank, bool shared_base, bool staged,
                  int cus, int* n_splits);
+// The plan of a prefill chunk that runs as a decode.
+void decode_chunk_plan(int64_t s_cap, int batch, int n_kv, int group, int head_dim, int rank, int cus, int* n_splits);
 // Whether a decode of `n_splits` splits a request cuts them by the requests'
 // lengths, over n_splits * batch workgroups, given room for twice as many
 // partials a row.

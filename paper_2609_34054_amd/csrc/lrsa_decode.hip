@@ -1498,6 +1498,23 @@ void decode_plan(int64_t s_cap, int batch, int n_kv, int group, int head_dim, in
   *n_splits = (int)ns;
 }
 
+// A chunk's splits are a decode's in the register-staged form, but at rank 64
+// no more than one of its workgroups per CU: they hold the whole register file,
+// so further ones queue, and a context short for its cache pays a start of
+// several microseconds for each round of them whether they find keys or not.
+// (4 tokens of 6 requests, 32 / 8 heads of dim 128, 64 of 65920 tokens: 19.7 us
+// as a prefill, 30.3 with four rounds, 18.2 so; 8192 of 8192: 73, 81 and 56.)
+void decode_chunk_plan(int64_t s_cap, int batch, int n_kv, int group, int head_dim, int rank, int cus, int* n_splits) {
+  decode_plan(s_cap, batch, n_kv, group, head_dim, rank, false, true, cus, n_splits);
+  if (rank < 64) return;
+  const int nw = dec_waves(rank);
+  const int64_t tiles = (s_cap + TK - 1) / TK, groups = (int64_t)(batch > 0 ? batch : 1) * ((n_kv + nw - 1) / nw);
+  const int64_t most = cus / groups > 1 ? cus / groups : 1;
+  if (*n_splits <= most) return;
+  const int64_t st = (tiles + most - 1) / most;
+  *n_splits = (int)((tiles + st - 1) / st);
+}
+
 // A paged rank-64 call takes the direct-V form where the register-staged one
 // would run splits of two tiles or more: at one tile there is nothing for the
 // extra waves to overlap with, and its longer start shows (1 request of 1024 /

@@ -439,6 +439,25 @@ def test_decode_split_count(batch, s_cap, splits):
     assert need == batch * 32 * splits * (4 + 128 + 16) * 4
 
 
+@pytest.mark.parametrize("batch,n_kv,s_cap,splits", [
+    (6, 8, 65920, 21),   # 12 workgroups a split: 252 of 256 CUs
+    (3, 8, 2048, 32),    # two tiles a split
+    (12, 8, 8192, 10),
+    (1, 8, 4096, 128),   # one tile a split
+    (128, 8, 4096, 1),
+    (5, 10, 65920, 17),  # three groups of heads
+])
+def test_rank_64_chunk_split_count(batch, n_kv, s_cap, splits):
+    """A chunk of a few tokens that runs as a decode at rank 64: at most one
+    workgroup (a request's four KV heads and split) per CU."""
+    group, n_tok = 4, 4
+    d = _dims(batch=batch, n_tok=n_tok, n_q_heads=group * n_kv, n_kv_heads=n_kv, s_cap=s_cap, rank=64,
+              kv_req_stride=s_cap * n_kv * 128, l_req_stride=s_cap * 64, b_req_stride=64 * n_kv * 128)
+    part = batch * n_tok * group * n_kv * (4 + 128 + 64) * 4
+    assert prc.lib().lr_shared_attention_workspace_size(ctypes.byref(d)) >= splits * part
+    assert prc.lib().lr_shared_attention_paged_workspace_size(ctypes.byref(d)) == splits * part
+
+
 def test_noalloc_checks_size_before_the_device():
     # The call with no workspace argument rejects a call whose split partials
     # exceed its static buffer on the host, before any device call.
