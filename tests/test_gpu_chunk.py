@@ -24,6 +24,9 @@ CASES = [
     ("g2_7_tokens_qv", 64, 32, 4, 2, 7, [97], 640, "v", "end"),
     ("g1_9_tokens_k_only", 64, 8, 9, 9, 9, [130], 512, "k", "end"),
     ("g4_4_tokens_below", 128, 16, 8, 2, 4, [300, 5], 448, "kv", "end"),  # short caches stay a prefill
+    # 16 splits, merged by a workgroup per row up to 2048 rows, by a wave above.
+    ("g4_4_tokens_2048_rows", 64, 16, 64, 16, 4, [512, 300, 64, 33, 32, 31, 5, 480], 512, "kv", "end"),
+    ("g4_4_tokens_2304_rows", 64, 16, 64, 16, 4, [512, 300, 64, 33, 32, 31, 5, 480, 100], 512, "kv", "end"),
     ("g4_2_tokens_plain", 128, 16, 8, 2, 2, [2000, 31], 2048, "none", "end"),
 ]
 
