@@ -450,7 +450,7 @@ namespace {
 // Partials of a chunk that runs as a decode (0: it does not).
 size_t chunk_decode_bytes(const lrsa_dims* dims, int rank, int cus, int* n_splits) {
   const int group = dims->n_q_heads / dims->n_kv_heads;
-  if (!prc::decode_takes_chunk(dims->s_cap, dims->n_tok, group)) return 0;
+  if (!prc::decode_takes_chunk(dims->s_cap, dims->batch, dims->n_tok, dims->n_kv_heads, group, dims->head_dim, rank, cus)) return 0;
   prc::decode_chunk_plan(dims->s_cap, dims->batch, dims->n_kv_heads, group, dims->head_dim, rank, cus, n_splits);
   return prc::decode_workspace_bytes(dims->batch * dims->n_tok, dims->n_q_heads, *n_splits, dims->head_dim, rank);
 }

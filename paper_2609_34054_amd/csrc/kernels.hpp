@@ -95,7 +95,7 @@ bool decode_direct_paged(int64_t s_cap, int batch, int n_tok, int n_kv, int head
 // Whether a prefill of this shape runs as a decode with several tokens (given
 // the workspace for its partials: batch * n_tok rows).  It never shares a base
 // between requests, and plans as paged calls do.
-bool decode_takes_chunk(int64_t s_cap, int n_tok, int group);
+bool decode_takes_chunk(int64_t s_cap, int batch, int n_tok, int n_kv, int group, int head_dim, int rank, int cus);
 size_t decode_workspace_bytes(int batch, int n_q, int n_splits, int head_dim, int rank);
 hipError_t launch_decode(const AttnArgs& a, hipStream_t stream);
 

@@ -1544,8 +1544,18 @@ bool decode_direct_paged(int64_t s_cap, int batch, int n_tok, int n_kv, int head
 // Not below 512 tokens, where a prefill has few tiles to walk and needs no
 // merge (3 tokens, group 4, rank 32, over 128 / 256 / 512 / 1024 keys: 12.6 /
 // 16.4 / 23.9 / 27.6 us as a prefill, 17.5 / 18.9 / 21.3 / 17.5 us so).
-bool decode_takes_chunk(int64_t s_cap, int n_tok, int group) {
-  return n_tok > 1 && n_tok * group <= 16 && s_cap >= 512;
+// Several requests at ranks 32 and 64, dim 128, only from 1024 tokens on, unless
+// a prefill would take more than one round of the CUs: their splits are one or
+// two tiles long and start with 32 or 64 KB of B_k (4 tokens of 12 requests, 512
+// tokens: rank 32, 64 / 256 / 512 keys 16.7 / 17.1 / 25.2 us as a prefill, 20.6
+// / 22.8 / 23.9 so; rank 64 17.2 / 18.5 / 28.2 and 23.3 / 25.0 / 27.7).  Where
+// few tokens of a small cache are in use the others lose a little too (12
+// requests, 64 / 256 / 512 of 512, rank 16: 16.8 / 17.1 / 23.8 and 16.6 / 18.6
+// / 19.1); the host does not know the lengths.
+bool decode_takes_chunk(int64_t s_cap, int batch, int n_tok, int n_kv, int group, int head_dim, int rank, int cus) {
+  if (n_tok < 2 || n_tok * group > 16) return false;
+  const bool several = (int64_t)batch * ((n_kv + 7) / 8) > 4 && (int64_t)batch * n_kv <= cus;
+  return s_cap >= (head_dim == 128 && rank >= 32 && several ? 1024 : 512);
 }
 
 size_t decode_workspace_bytes(int batch, int n_q, int n_splits, int head_dim, int rank) {

@@ -458,6 +458,25 @@ def test_rank_64_chunk_split_count(batch, n_kv, s_cap, splits):
     assert prc.lib().lr_shared_attention_paged_workspace_size(ctypes.byref(d)) == splits * part
 
 
+@pytest.mark.parametrize("batch,rank,head_dim,s_cap,chunk", [
+    (12, 32, 128, 512, False), (12, 64, 128, 1023, False), (12, 32, 128, 1024, True),
+    (4, 64, 128, 512, True), (4, 64, 128, 511, False), (5, 64, 128, 512, False),
+    (33, 32, 128, 512, True),   # 264 units: a prefill of two rounds
+    (12, 16, 128, 512, True), (12, 64, 64, 512, True),
+])
+def test_chunk_form_by_capacity(batch, rank, head_dim, s_cap, chunk):
+    """Which chunks of a few tokens ask for the partials of a split decode: 8 KV
+    heads and 256 CUs; the others need those of a prefill, here none or few."""
+    d = _dims(batch=batch, n_tok=4, head_dim=head_dim, s_cap=s_cap, rank=rank, kv_req_stride=s_cap * 8 * head_dim,
+              l_req_stride=s_cap * rank, b_req_stride=rank * 8 * head_dim)
+    L, part = prc.lib(), batch * 4 * 32 * (4 + head_dim + rank) * 4
+    st = L.lr_shared_attention(ctypes.byref(d), A16, A16, A16, A16, A16, A16, A16, A16, A16, A16, None, None, 0, None)
+    m = re.search(r"(\d+) needed", L.prc_last_error().decode())
+    need = int(m.group(1)) if st == EWS else 0  # what the prefill insists on
+    asked = L.lr_shared_attention_paged_workspace_size(ctypes.byref(d))
+    assert (asked > need) == chunk and asked % part == 0
+
+
 def test_noalloc_checks_size_before_the_device():
     # The call with no workspace argument rejects a call whose split partials
     # exceed its static buffer on the host, before any device call.
