@@ -1343,14 +1343,14 @@ __global__ void __launch_bounds__(64 * MR_ROWS) lrsa_merge_rows_kernel(const Att
 template <int D, int R>
 hipError_t launch_merge_t(const AttnArgs& a, hipStream_t st) {
   const int64_t n_rows = (int64_t)a.batch * a.n_tok * a.n_q;
-  // Chunks and shared-base calls of few rows take a workgroup per row from 8
-  // splits on: one wave's reads of B_v and of the splits are a chain as long as
+  // Chunks and shared-base calls of few rows take a workgroup per row with few
+  // splits too: one wave's reads of B_v and of the splits are a chain as long as
   // the rank, and too few rows run side by side to hide it (4 tokens of 4
   // requests over 512 keys, dim 128, one wave / four: rank 16 19.9 / 15.7 us, 32
-  // 23.5 / 18.5; 8 requests of 500 over one base, rank 64, 26.2 / 20.5).  More
-  // rows or fewer splits: 100 requests, 1600 rows of 5 splits 11.0 / 12.1; 2560
-  // rows of 6 splits, rank 64, 23.9 / 26.7.
-  const bool few_rows = a.dec_group != 0 && (a.n_tok > 1 || a.dec_shared) && n_rows <= 2048 && a.n_splits >= 8;
+  // 23.5 / 18.5; 8 requests over one base, rank 64, of 500 tokens 26.2 / 20.5,
+  // of 64, two splits, 20.7 / 18.3).  Not more rows: 100 requests, 1600 rows of 5
+  // splits 11.0 / 12.1; 2560 rows of 6 splits, rank 64, 23.9 / 26.7.
+  const bool few_rows = a.dec_group != 0 && (a.n_tok > 1 || a.dec_shared) && n_rows <= (a.n_splits >= 8 ? 2048 : 1024);
   if (a.n_splits <= 16 && !few_rows) {
     hipLaunchKernelGGL((lrsa_merge_rows_kernel<D, R>), dim3((unsigned)((n_rows + MR_ROWS - 1) / MR_ROWS)),
                        dim3(64 * MR_ROWS), 0, st, a, n_rows);
