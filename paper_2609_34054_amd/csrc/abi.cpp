@@ -488,23 +488,21 @@ size_t workspace_size(const lrsa_dims* dims, bool paged, bool optional = true) {
   // Paged caches always take the per-request decode kernel (requests may share
   // some blocks and not others); the size covers either of its forms (the
   // register-staged one has at least as many splits).
-  const bool shared = !paged && prc::decode_shares_base(dims->s_cap, dims->batch, dims->kv_req_stride);
-  prc::decode_plan(dims->s_cap, dims->batch, dims->n_kv_heads, dims->n_q_heads / dims->n_kv_heads, dims->head_dim, r,
-                   shared, paged, plan_cus(), &n_splits);
+  const int cus = plan_cus(), group = dims->n_q_heads / dims->n_kv_heads;
+  const bool shared = !paged && prc::decode_shares_base(dims->s_cap, dims->batch, dims->kv_req_stride, dims->n_kv_heads, group,
+                                                        dims->head_dim, r, cus);
+  prc::decode_plan(dims->s_cap, dims->batch, dims->n_kv_heads, group, dims->head_dim, r, shared, paged, cus, &n_splits);
   if (optional) {
     // Room for splits balanced over the requests (paged: in the form with the
     // longer splits, which it takes unless its block tables are very long).
     int ns = 0;
-    prc::decode_plan(dims->s_cap, dims->batch, dims->n_kv_heads, dims->n_q_heads / dims->n_kv_heads, dims->head_dim, r,
-                     shared, false, plan_cus(), &ns);
+    prc::decode_plan(dims->s_cap, dims->batch, dims->n_kv_heads, group, dims->head_dim, r, shared, false, cus, &ns);
     if (prc::decode_balances(dims->s_cap, dims->batch, dims->n_tok, dims->head_dim, r, ns, shared, false) && 2 * ns > n_splits)
       n_splits = 2 * ns;
-  } else if (!paged && !shared && prc::decode_can_share_base(dims->batch, dims->kv_req_stride)) {
-    // A short shared base takes the shared kernel after all where only its
-    // partials fit.
+  } else if (!paged && prc::decode_base_is_short(dims->s_cap, dims->batch, dims->kv_req_stride)) {
+    // A short shared base takes the other kernel where only its partials fit.
     int ns = 0;
-    prc::decode_plan(dims->s_cap, dims->batch, dims->n_kv_heads, dims->n_q_heads / dims->n_kv_heads, dims->head_dim, r,
-                     true, false, plan_cus(), &ns);
+    prc::decode_plan(dims->s_cap, dims->batch, dims->n_kv_heads, group, dims->head_dim, r, !shared, false, cus, &ns);
     if (ns < n_splits) n_splits = ns;
   }
   return prc::decode_workspace_bytes(dims->batch, dims->n_q_heads, n_splits, dims->head_dim, r);
@@ -539,13 +537,13 @@ prc_status attention_impl(const char* who, const lrsa_dims* dims, const lrsa_pag
 #if PRC_DEVICE_CHECKS
     if (prc_status dc = device_data_check(who, positions, kv_len, a.batch, a.n_tok, a.s_cap, st)) return dc;
 #endif
-    bool shared = pg == nullptr && prc::decode_shares_base(a.s_cap, a.batch, a.kv_stride);
+    bool shared = pg == nullptr && prc::decode_shares_base(a.s_cap, a.batch, a.kv_stride, a.n_kv, a.group, a.head_dim, a.rank, cus);
     a.dec_direct = pg != nullptr && prc::decode_direct_paged(a.s_cap, a.batch, a.n_tok, a.n_kv, a.head_dim, a.rank, a.max_blk, cus);
     const bool staged = pg != nullptr && !a.dec_direct;
     prc::decode_plan(a.s_cap, a.batch, a.n_kv, a.group, a.head_dim, a.rank, shared, staged, cus, &a.n_splits);
-    if (pg == nullptr && !shared && prc::decode_can_share_base(a.batch, a.kv_stride) &&
+    if (pg == nullptr && prc::decode_base_is_short(a.s_cap, a.batch, a.kv_stride) &&
         workspace_bytes < prc::decode_workspace_bytes(a.batch, a.n_q, a.n_splits, a.head_dim, a.rank)) {
-      shared = true;
+      shared = !shared;
       prc::decode_plan(a.s_cap, a.batch, a.n_kv, a.group, a.head_dim, a.rank, shared, staged, cus, &a.n_splits);
     }
     a.dec_shared = shared;

@@ -74,8 +74,11 @@ int decode_tile_tokens();
 // A decode batch whose requests all read one base cache (request stride 0)
 // can run the shared-base kernel: each base tile is read once for all of them.
 bool decode_can_share_base(int batch, int64_t kv_req_stride);
+// Whether that base is so short that either kernel may run.
+bool decode_base_is_short(int64_t s_cap, int batch, int64_t kv_req_stride);
 // Whether it does, given the workspace of the form it then takes.
-bool decode_shares_base(int64_t s_cap, int batch, int64_t kv_req_stride);
+bool decode_shares_base(int64_t s_cap, int batch, int64_t kv_req_stride, int n_kv, int group, int head_dim, int rank,
+                        int cus);
 // `cus`: compute units of the device the call runs on; `staged`: the call
 // takes the form with V staged in registers where the rank has two (paged
 // calls with long block tables, several query tokens).  The

@@ -1441,14 +1441,33 @@ hipError_t launch_r(const AttnArgs& a, hipStream_t st, bool shared) {
 
 int decode_tile_tokens() { return TK; }
 
+// Workgroups of the shared-base kernel for one split.
+static int64_t shared_workgroups(int64_t batch, int n_kv, int group, int rank) {
+  const int64_t rq = sh_rpb(group) * (batch > sh_rpb(group) ? sh_groups(rank) : 1);
+  return (int64_t)n_kv * ((batch + rq - 1) / rq);
+}
+
 // Below 2048 tokens the base tiles stay in the L2 whoever reads them, and the
 // shared-base kernel's longer start costs more than its one read saves (8 / 2 /
 // 16 requests of 300 tokens: 19.3 / 16.5 / 21.4 us shared, 16.6 / 14.9 / 18.4
 // each by itself; of 1200: 19.0 / 14.8 / 25.9 and 17.9 / 13.9 / 25.6; 8 of 2400:
 // 21.9 and 23.0).
 bool decode_can_share_base(int batch, int64_t kv_req_stride) { return batch > 1 && kv_req_stride == 0; }
-bool decode_shares_base(int64_t s_cap, int batch, int64_t kv_req_stride) {
-  return decode_can_share_base(batch, kv_req_stride) && s_cap >= 2048;
+bool decode_base_is_short(int64_t s_cap, int batch, int64_t kv_req_stride) {
+  return decode_can_share_base(batch, kv_req_stride) && s_cap < 2048;
+}
+// At rank 64, dim 128, the per-request kernel's own start is the longer one (its
+// heads' 64 KB of B_k): there the shared kernel runs at every size where one
+// round of its workgroups holds the call (2 / 8 / 16 requests of 300 tokens, 32
+// / 8 heads: 26.3 / 27.0 / 30.3 us each by itself, 17.2 / 19.3 / 20.8 shared; 8
+// of 700 with 40 / 8 heads, 264 workgroups: 24.7 and 28.3).
+bool decode_shares_base(int64_t s_cap, int batch, int64_t kv_req_stride, int n_kv, int group, int head_dim, int rank, int cus) {
+  if (!decode_can_share_base(batch, kv_req_stride)) return false;
+  if (!decode_base_is_short(s_cap, batch, kv_req_stride)) return true;
+  if (!dec_vdma(head_dim, rank, false)) return false;
+  int ns;
+  decode_plan(s_cap, batch, n_kv, group, head_dim, rank, true, false, cus, &ns);
+  return ns * shared_workgroups(batch, n_kv, group, rank) <= cus;
 }
 
 // The one-round kernel has nothing left to even out requests of different
@@ -1469,8 +1488,7 @@ void decode_plan(int64_t s_cap, int batch, int n_kv, int group, int head_dim, in
   const int64_t nb = batch > 0 ? batch : 1;
   // Workgroups per split: (request, group of nw KV heads) for the per-request
   // kernel, (KV head, groups of requests) when the base cache is shared.
-  const int64_t rq = sh_rpb(group) * (nb > sh_rpb(group) ? sh_groups(rank) : 1);
-  const int64_t groups = shared_base ? (int64_t)n_kv * ((nb + rq - 1) / rq) : nb * ((n_kv + nw - 1) / nw);
+  const int64_t groups = shared_base ? shared_workgroups(nb, n_kv, group, rank) : nb * ((n_kv + nw - 1) / nw);
   // Splits for a target of `rounds` 8-wave workgroups per CU.
   auto plan = [&](int64_t rounds, int64_t* ns_out, int64_t* st_out) {
     const int64_t target_wgs = rounds * (cus > 0 ? cus : 1) * 8 / nw;

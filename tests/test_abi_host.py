@@ -477,6 +477,35 @@ def test_chunk_form_by_capacity(batch, rank, head_dim, s_cap, chunk):
     assert (asked > need) == chunk and asked % part == 0
 
 
+@pytest.mark.parametrize("batch,n_q,rank,head_dim,s_cap,shared", [
+    (2, 32, 64, 128, 300, True), (16, 32, 64, 128, 300, True), (8, 40, 64, 128, 500, True),
+    (8, 40, 64, 128, 700, False),   # 264 workgroups of the shared kernel
+    (8, 32, 16, 128, 2047, False), (8, 32, 16, 128, 2048, True), (8, 32, 64, 64, 300, False),
+])
+def test_short_shared_base_form(batch, n_q, rank, head_dim, s_cap, shared):
+    """Requests over one short base: the kernel a decode takes, seen by the splits
+    its workspace holds (8 KV heads, 256 CUs), and the least it insists on (the
+    smaller of both kernels' partials below 2048 tokens)."""
+    d = _dims(batch=batch, n_tok=1, n_q_heads=n_q, head_dim=head_dim, s_cap=s_cap, rank=rank, kv_req_stride=0,
+              l_req_stride=s_cap * rank, b_req_stride=rank * 8 * head_dim)
+    tiles, per = -(-s_cap // 32), {4: 4, 5: 3}[n_q // 8]
+    groups = 8 * -(-batch // (per * (2 if batch > per and rank < 64 else 1)))
+
+    def splits(target, wgs):
+        ns = max(1, min(-(-target // wgs), tiles))
+        return -(-tiles // -(-tiles // ns))
+    nw = 4 if rank == 64 else 8
+    one, own = splits(256, groups), splits(256 * 8 // nw, batch * (8 // nw))
+    part = batch * n_q * (4 + head_dim + rank) * 4
+    L = prc.lib()
+    full = L.lr_shared_attention_workspace_size(ctypes.byref(d)) // part
+    assert full >= (one if shared else own) and (full == one or not shared)
+    assert L.lr_shared_attention(ctypes.byref(d), A16, A16, A16, A16, A16, A16, A16, A16, A16, A16, None, None, 0,
+                                 None) == EWS
+    need = int(re.search(r"(\d+) needed", L.prc_last_error().decode()).group(1))
+    assert need == (min(one, own) if s_cap < 2048 else one) * part
+
+
 def test_noalloc_checks_size_before_the_device():
     # The call with no workspace argument rejects a call whose split partials
     # exceed its static buffer on the host, before any device call.
