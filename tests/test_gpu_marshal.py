@@ -28,11 +28,31 @@ def _attention(g, **kw):
                                    a["positions"], a["kv_len"], rope_theta=1e4, want_lse=True, **rest)
 
 
-def _both(call, monkeypatch):
-    """The call through the native module and through the Python checks."""
+class _Spy:
+    """The native module's functions, and the kind of each one's last answer."""
+
+    def __init__(self, m):
+        self.last = None
+        for name in ("attention", "paged", "project", "project_paged"):
+            setattr(self, name, self._watch(getattr(m, name)))
+
+    def _watch(self, f):
+        def g(*a):
+            r = f(*a)
+            self.last = type(r)
+            return r
+        return g
+
+
+def _both(call, monkeypatch, answer=int):
+    """The call through the native module and through the Python checks.
+    ``answer``: the type of what the module returns, ``int`` for a call that it
+    makes itself (whatever the status), NoneType for one it leaves to Python."""
     got = []
     for native in (True, False):
         with monkeypatch.context() as m:
+            spy = _Spy(binding._native().m)
+            m.setattr(binding._native(), "m", spy)
             if not native:
                 m.setattr(binding, "_on_gpu", lambda t: False)
             try:
@@ -41,7 +61,11 @@ def _both(call, monkeypatch):
                 got.append([t.clone() for t in out if t is not None])
             except Exception as e:  # noqa: BLE001
                 got.append((type(e), str(e)))
+            assert spy.last is (answer if native else None), (native, spy.last)
     return got
+
+
+NOT_TAKEN = type(None)
 
 
 @pytest.mark.parametrize("n_tok", [1, 3, 40])
@@ -67,11 +91,11 @@ def test_attention_calls_agree(n_tok, monkeypatch):
         g["Q"], pl["K_base"], pl["V_base"], pl["L_k"], pl["L_v"], g["B_k"], g["B_v"], g["positions"], g["kv_len"],
         tbl.cuda(), rope_theta=1e4, want_lse=True), monkeypatch)
     assert all(torch.equal(x, y) for x, y in zip(a, b))
-    O = torch.empty_like(g["Q"])
+    # O holds a sentinel before each leg: the second must not see the first's.
     a, b = _both(lambda: prc.lr_shared_attention_noalloc(
         g["Q"], g["K_base"], g["V_base"], g["L_k"], g["L_v"], g["B_k"], g["B_v"], g["positions"], g["kv_len"],
-        rope_theta=1e4, O=O), monkeypatch)
-    assert torch.equal(a[0], b[0])
+        rope_theta=1e4, O=torch.full_like(g["Q"], 9.0)), monkeypatch)
+    assert torch.equal(a[0], b[0]) and not (a[0] == 9.0).all()
 
 
 def test_refusals_agree(monkeypatch):
@@ -81,13 +105,16 @@ def test_refusals_agree(monkeypatch):
            dict(positions=g["positions"].long()), dict(kv_len=g["kv_len"][:1]), dict(B_k=g["B_k"][:, :8]),
            dict(L_k=None), dict(Q=g["Q"].transpose(1, 2)), dict(rope_theta=-1.0), dict(Q=g["Q"][0]),
            dict(L_v=g["L_v"].transpose(1, 2)), dict(kv_len=None), dict(Q=g["Q"][:, :, :7])]
-    for kw in bad:
+    # Refused by the library (missing L_k, RoPE base, head count); a Q of three
+    # dims does not reach the module.
+    answers = {6: int, 8: int, 9: None, 12: int}
+    for i, kw in enumerate(bad):
         def call(kw=kw):
             a = dict(g, rope_theta=1e4)
             a.update(kw)
             return prc.lr_shared_attention(a["Q"], a["K_base"], a["V_base"], a["L_k"], a["L_v"], a["B_k"], a["B_v"],
                                            a["positions"], a["kv_len"], rope_theta=a["rope_theta"])
-        a, b = _both(call, monkeypatch)
+        a, b = _both(call, monkeypatch, answers.get(i, NOT_TAKEN))
         assert isinstance(a, tuple) and a == b, (kw.keys(), a, b)
 
 
@@ -114,8 +141,8 @@ def test_projection_calls_agree(monkeypatch):
                                                z(2, N, 16, r), rope_theta=1e4),
            lambda: prc.project_kv_and_lr_cache_paged(X, W, A, n_kv, d, 2, N, r, z(3, 64, n_kv, d), z(3, 64, n_kv, d),
                                                      z(2, N, 3, 64, r), tbl.long(), rope_theta=1e4)]
-    for call in bad:
-        a, b = _both(call, monkeypatch)
+    for i, call in enumerate(bad):
+        a, b = _both(call, monkeypatch, int if i == 0 else NOT_TAKEN)
         assert isinstance(a, tuple) and a == b, (a, b)
 
 
@@ -140,5 +167,5 @@ def test_nested_tensors_are_refused(monkeypatch):
                  lambda: prc.precompute_lr_cache(nest(z), z, 1, 1, 8, L),
                  lambda: prc.project_kv_and_lr_cache_paged(nest(z), z, z, 1, 64, 1, 1, 8, pool, pool, L, tbl[0],
                                                            rope_theta=1e4)):
-        a, b = _both(call, monkeypatch)
+        a, b = _both(call, monkeypatch, NOT_TAKEN)
         assert isinstance(a, tuple) and a == b, (a, b)
