@@ -231,13 +231,20 @@ typedef struct lrsa_dims {
  *              modelled time (rounds of one unit per CU) by at least 10%.
  *              For a chunk of at most 16 (token, head) pairs per KV head
  *              (n_tok * n_q / n_kv <= 16) over at least 512 tokens of capacity
- *              the size covers partials that let it run as a decode, split
- *              over the keys; given less, or NULL, it runs as any other prefill.
+ *              (several requests at rank 32 or 64 and d = 128: 1024) the size
+ *              covers partials that let it run as a decode, split over the
+ *              keys; given less, or NULL, it runs as any other prefill.
  *              For a rank-64 decode of several requests (d = 128) the size has
  *              room for splits balanced over their lengths, and for requests
- *              that share a base of under 2048 tokens for each to run by
- *              itself; such calls are also taken with less, down to the
- *              partials of even splits, or of the shared form.
+ *              that share a base of under 2048 tokens for the faster of two
+ *              kernels (each request by itself, or all together); such calls
+ *              are also taken with less, down to the partials of even splits,
+ *              or of the other kernel.
+ *              So the size given can decide how a call is split, and how it is
+ *              split decides the order of its fp32 sums: the last bits of a
+ *              result are those of this size.  In balanced splits and over a
+ *              shared base a request's splits, and with them its last bits,
+ *              also depend on the lengths of the other requests.
  *              For a prefill of rank 8, 16, 32 or 64 with at least 8 row
  *              tiles (256 query rows each) per KV head, d = 128 and
  *              contiguous caches, the size also covers an optional tile
@@ -277,9 +284,15 @@ size_t lr_shared_attention_workspace_size(const lrsa_dims* dims);
  * PRC_NOALLOC_WORKSPACE_BYTES that the library holds on each device it runs
  * on until the process ends (its device address is fetched on the first call
  * made with that device current).  The call allocates nothing.
- *   - A call whose partials (lr_shared_attention_workspace_size(dims)) exceed
- *     PRC_NOALLOC_WORKSPACE_BYTES returns PRC_EWORKSPACE and launches nothing.
- *   - Every call on one device shares that device's array.  No part of it
+ *   - A call whose partials exceed PRC_NOALLOC_WORKSPACE_BYTES even at the
+ *     least that lr_shared_attention insists on (which leaves out the parts of
+ *     lr_shared_attention_workspace_size that a call can do without) returns
+ *     PRC_EWORKSPACE and launches nothing.  Calls take the parts that fit, so
+ *     their splits, and the last bits, can differ from those of a call with the
+ *     recommended workspace.
+ *   - A call that insists on no partials (a prefill that needs no split, also a
+ *     chunk of a few tokens) does not use the array.  All others on one device
+ *     share that device's.  No part of it
  *     needs to start at zero (each split writes all of its partial before the
  *     merge reads it), but calls that overlap on one device, on different
  *     streams or from different threads, race on it: order them on one stream.
@@ -310,10 +323,14 @@ typedef struct lrsa_paging {
  * with chunked prefill: the n_tok
  * queries of a chunk attend over every earlier token plus the chunk itself,
  * once the chunk has been written with project_kv_and_lr_cache_paged).
- * Computes exactly what lr_shared_attention computes (bit for bit, given the
- * same cache contents) with token t of request b read from row
- * t % block_size of block kv_block_table[b][t / block_size] (base) and
- * lr_block_table[b][t / block_size] (LR).
+ * Computes what lr_shared_attention computes with token t of request b read
+ * from row t % block_size of block kv_block_table[b][t / block_size] (base) and
+ * lr_block_table[b][t / block_size] (LR): bit for bit, given the same cache
+ * contents and no less than the recommended workspace, except where the two
+ * take different kernels and sum in another order: a decode over a base that
+ * contiguous requests share, a rank-64 decode (d = 128) whose tables have more
+ * than 2048 entries a request or whose splits are one 32-token tile, and a
+ * contiguous prefill that uses the tile cache.
  *
  *   K_pool, V_pool  [n_kv_blocks, block_size, n_kv, d] bf16; request b's pool
  *              starts kv_req_stride * b elements in (normally 0: one pool
