@@ -69,7 +69,7 @@ struct AttnArgs {
   double w2pi[kMaxHalfDim];  // RoPE omega_j / (2 pi), fp64
 };
 
-// Decode (one query token per request): split-KV partials + merge.
+// Decode (one query token per request, or a chunk of a few): split-KV partials + merge.
 int decode_tile_tokens();
 // A decode batch whose requests all read one base cache (request stride 0)
 // can run the shared-base kernel: each base tile is read once for all of them.
@@ -97,7 +97,7 @@ bool decode_balances(int64_t s_cap, int batch, int n_tok, int head_dim, int rank
 bool decode_direct_paged(int64_t s_cap, int batch, int n_tok, int n_kv, int head_dim, int rank, int max_blk, int cus);
 // Whether a prefill of this shape runs as a decode with several tokens (given
 // the workspace for its partials: batch * n_tok rows).  It never shares a base
-// between requests, and plans as paged calls do.
+// between requests, and takes the register-staged form.
 bool decode_takes_chunk(int64_t s_cap, int batch, int n_tok, int n_kv, int group, int head_dim, int rank, int cus);
 size_t decode_workspace_bytes(int batch, int n_q, int n_splits, int head_dim, int rank);
 hipError_t launch_decode(const AttnArgs& a, hipStream_t stream);

@@ -1,4 +1,5 @@
-// LR-shared attention, decode (one query token per request), gfx950.
+// LR-shared attention, decode (one query token per request, or a chunk of a few
+// whose (token, head) pairs per KV head fit 16 columns), gfx950.
 //
 // Reuse step of PreLRShared (Sec. 3.1): the current agent attends over the
 // shared base cache plus its own rank-r LR cache.  Keys are rebuilt on chip,
@@ -29,9 +30,10 @@
 //      operand layout, needs no shuffles and the softmax rescale is a
 //      per-lane scalar.
 // The loads of the next sub-block (the next two in the 4-wave rank-64
-// kernel) are in flight while the current one is consumed.  The contiguous
-// rank-64 kernel at d = 128 sends its V rows straight to LDS (direct
-// global->LDS loads into a two-buffer ring) instead of through registers.
+// kernel) are in flight while the current one is consumed.  The direct form of
+// the rank-64 kernel at d = 128 (contiguous calls and most paged ones, one query
+// token) sends its V rows straight to LDS (direct global->LDS loads into a
+// two-buffer ring) instead of through registers.
 #include "common.hpp"
 #include "kernels.hpp"
 #include "rebuild.hpp"
@@ -138,15 +140,16 @@ __device__ __forceinline__ int tiles_per_split(int vis, int n_splits) {
   return st < 1 ? 1 : st;
 }
 // The furthest end among the requests whose splits cover the same ranges
-// (one request, or the dec_group <= 64 requests of a shared-base workgroup).
-// Lane i reads request i's length and position, so the reads run side by side;
-// `mine` receives its visible keys (0 past the group or the batch).
+// (one request, or the dec_group <= kMaxGroup requests of a shared-base
+// workgroup).  Lane i reads request i's length and position, so the reads run
+// side by side; `mine` receives its visible keys (0 past the group or the batch).
+constexpr int kMaxGroup = 8;  // a power of two: the lanes the maximum is taken over
 __device__ __forceinline__ int group_visible_keys(const AttnArgs& a, int b, int grp, int lane, int& mine) {
   const int r = b / grp * grp + lane;
   mine = lane < grp && r < a.batch ? visible_keys(a, r) : 0;
   int vis = mine;
 #pragma unroll
-  for (int x = 1; x < 8; x <<= 1) vis = max(vis, __shfl_xor(vis, x, 64));
+  for (int x = 1; x < kMaxGroup; x <<= 1) vis = max(vis, __shfl_xor(vis, x, 64));
   return __builtin_amdgcn_readfirstlane(vis);
 }
 
@@ -844,9 +847,9 @@ lrsa_merge_kernel(const AttnArgs a) {
 // waits for another wave.  The B_k^T fragments of all the workgroup's requests
 // wait in LDS.  The partials go to the same workspace and the same merge.
 //
-// Eight agents over 32k tokens, 8 KV heads, rank 16: 97 us per call with one
+// Eight agents over 32k tokens, 8 KV heads, rank 16: 90 us per call with one
 // request per wave (12 of 16 columns empty, softmax and P V repeated per
-// request), 67 us with four.  What is left is vector work: 510 vector
+// request), 66 us with four.  What is left is vector work: about 510 vector
 // instructions per sub-block of four requests, 336 of them the rotation of
 // the expansions, at two waves per SIMD half of the cycles.  Measured and no
 // better: two sub-blocks of loads in flight (256 registers; 72 us), base rows
@@ -894,7 +897,7 @@ lrsa_decode_shared_kernel(const AttnArgs a, int n_grp) {
   const bool has_lk = a.Lk != nullptr, has_lv = a.Lv != nullptr;
   // The split's range divides the furthest end among the workgroup's
   // requests; each request stops at its own.
-  static_assert(sh_groups(R) * RPB <= 8, "one reduction over 8 lanes");
+  static_assert(sh_groups(R) * RPB <= kMaxGroup, "one reduction over the lanes of a group");
   int vis_lane;
   const int vis_wg = group_visible_keys(a, b_wg, n_grp * RPB, lane, vis_lane);
   const int st_tiles = __builtin_amdgcn_readfirstlane(tiles_per_split(vis_wg, a.n_splits));
@@ -1398,6 +1401,7 @@ hipError_t launch_shared_rpb(AttnArgs a, hipStream_t st) {
   // One group of requests needs all eight waves as streams; more go two to a
   // workgroup where their B_k fits.
   const int n_grp = a.batch > RPB ? sh_groups(R) : 1;
+  static_assert(sh_groups(R) * RPB <= kMaxGroup, "group_visible_keys covers it");
   a.dec_group = n_grp * RPB;
   const dim3 grid(a.n_splits, a.n_kv, (a.batch + a.dec_group - 1) / a.dec_group);
   hipLaunchKernelGGL((lrsa_decode_shared_kernel<D, R, RPB>), grid, dim3(SH_W * 64), 0, st, a, n_grp);
@@ -1451,7 +1455,10 @@ static int64_t shared_workgroups(int64_t batch, int n_kv, int group, int rank) {
 // shared-base kernel's longer start costs more than its one read saves (8 / 2 /
 // 16 requests of 300 tokens: 19.3 / 16.5 / 21.4 us shared, 16.6 / 14.9 / 18.4
 // each by itself; of 1200: 19.0 / 14.8 / 25.9 and 17.9 / 13.9 / 25.6; 8 of 2400:
-// 21.9 and 23.0).
+// 21.9 and 23.0).  The line is on the capacity, as the host does not know the
+// lengths; a short context in a large cache stays near its own size's time,
+// since its splits divide the keys in use (rank 16, 300 of 65920 tokens, 2 / 8 /
+// 16 requests: 13.0 / 15.5 / 16.5 us).
 bool decode_can_share_base(int batch, int64_t kv_req_stride) { return batch > 1 && kv_req_stride == 0; }
 bool decode_base_is_short(int64_t s_cap, int batch, int64_t kv_req_stride) {
   return decode_can_share_base(batch, kv_req_stride) && s_cap < 2048;
@@ -1546,6 +1553,10 @@ void decode_chunk_plan(int64_t s_cap, int batch, int n_kv, int group, int head_d
 // extra waves to overlap with, and its longer start shows (1 request of 1024 /
 // 2048 tokens: 19.9 / 22.0 us staged, 24.9 / 25.8 direct; 3: 22.4 / 34.2 and
 // 26.1 / 26.8; 8: 35.2 / 41.6 and 28.0 / 33.7; 1 of 8192: 36.1 and 28.9).
+// The line is on the capacity; a short context in a large cache pays the direct
+// form's start, but not the staged form's rounds of workgroups without keys (1 /
+// 3 / 8 requests of 256 of 65920 tokens: 42.4 / 61.6 / 63.1 us staged, in splits
+// of the capacity, and 23.0 / 24.8 / 25.5).
 bool decode_direct_paged(int64_t s_cap, int batch, int n_tok, int n_kv, int head_dim, int rank, int max_blk, int cus) {
   if (!dec_vdma(head_dim, rank, false) || n_tok != 1 || max_blk > kLdsBlocks) return false;
   const int nw = dec_nw(head_dim, rank, true);

@@ -373,11 +373,11 @@ hipError_t launch_tb(const PrecomputeArgs& a, hipStream_t st) {
 // a transposing read serves together (two groups of four, 8 rows apart) hit
 // different banks.  A unit holds 16 value or LR columns, or 8 key dims and
 // their 8 RoPE partners (which land in lanes l and l ^ 32 of the result).
-// 4096 x 2304, d_in 4096: 107 us with 128 x 128 tiles, 71 us (1.09 PFLOP/s)
+// 4096 x 2304, d_in 4096: 107 us with 128 x 128 tiles, 69 us (1.12 PFLOP/s)
 // with 256 x 160; alone on its CU a 256 x 160 tile takes 56 us, 33 of them
 // MFMAs at their full rate and about 10 before the first stage and after the
-// last.  Measured and slower: fragments read at the head of each stage instead
-// of between the MFMAs of the step before (77 us); the compute waves issuing
+// last.  Measured and slower (against 71 then): fragments read at the head of
+// each stage instead of between the MFMAs of the step before (77 us); the compute waves issuing
 // the weight loads (80 us: a full load queue stalls their MFMAs too).
 constexpr int WD_TT = 256;  // tokens per workgroup
 constexpr int WD_KS = 64;   // k per stage
@@ -897,7 +897,7 @@ hipError_t launch_precompute(const PrecomputeArgs& a, hipStream_t st) {
   // 600 tiles).  64 x 64 and 128 x 128 tiles are bound by the CU's load rate,
   // the 256-token ones by their MFMAs.  Over rounds that are nearly empty the
   // smaller tile wins (1000 tokens x 2304 columns: 57, 35, 48, 56, 65 us in
-  // this order), over full ones the larger (4096 x 2304: 188, 107, 93, 97, 71
+  // this order), over full ones the larger (4096 x 2304: 188, 107, 93, 97, 69
   // us; 2048 x 2816, d_in 5120: 148, 86, 67, 60, 71 us).  128-wide tiles need
   // the K/V boundary on a tile edge; 256-token tiles need their rows of X within
   // the 31 bits of their byte offsets (INT32_MIN, past them, marks what is not read).
