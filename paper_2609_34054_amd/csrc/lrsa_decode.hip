@@ -1467,7 +1467,7 @@ bool decode_base_is_short(int64_t s_cap, int batch, int64_t kv_req_stride) {
 // heads' 64 KB of B_k): there the shared kernel runs at every size where one
 // round of its workgroups holds the call (2 / 8 / 16 requests of 300 tokens, 32
 // / 8 heads: 26.3 / 27.0 / 30.3 us each by itself, 17.2 / 19.3 / 20.8 shared; 8
-// of 700 with 40 / 8 heads, 264 workgroups: 24.7 and 28.3).
+// of 700 with 40 / 8 heads: 24.7 and 20.1).
 bool decode_shares_base(int64_t s_cap, int batch, int64_t kv_req_stride, int n_kv, int group, int head_dim, int rank, int cus) {
   if (!decode_can_share_base(batch, kv_req_stride)) return false;
   if (!decode_base_is_short(s_cap, batch, kv_req_stride)) return true;
@@ -1512,6 +1512,13 @@ void decode_plan(int64_t s_cap, int batch, int n_kv, int group, int head_dim, in
     int64_t st = (tiles + ns - 1) / ns;
     if (st < 1) st = 1;
     ns = (tiles + st - 1) / st;
+    // One round is kept to one: workgroups past it wait for a whole round as soon
+    // as their XCD has no CU left for them, which is up to the lengths (12 paged
+    // requests of 4736 tokens of capacity, rank 8, 264 / 252 workgroups: of 3100
+    // tokens each 37.4 / 37.3 us, of 3100, 3036, .. 46.4 / 35.6, of 4736 72.5 /
+    // 49.6).  The splits in use may then be a tile longer (24 requests of 1320,
+    // 1280, .. of 2000 tokens: 32.1 / 34.5).
+    if (rounds == 1 && groups * ns > target_wgs && groups <= target_wgs) ns = target_wgs / groups;
     *ns_out = ns < 1 ? 1 : ns;
     *st_out = st;
   };

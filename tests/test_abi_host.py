@@ -432,6 +432,10 @@ def test_prefill_split_count(n_tok, n_q, s_cap, splits):
     (1, 36864, 231),   # two rounds would cut splits to 3 tiles: one round
     (1, 66048, 230),
     (1, 4480, 140),    # one 32-token tile per split
+    (12, 4736, 21),    # 252 workgroups; 22 splits would be 264, a second round
+    (11, 1500, 23),
+    (24, 2000, 10),
+    (300, 400, 1),     # more requests than CUs
 ])
 def test_decode_split_count(batch, s_cap, splits):
     d = _dims(batch=batch, n_tok=1, s_cap=s_cap, kv_req_stride=s_cap * 8 * 128, l_req_stride=s_cap * 16)
@@ -479,7 +483,8 @@ def test_chunk_form_by_capacity(batch, rank, head_dim, s_cap, chunk):
 
 @pytest.mark.parametrize("batch,n_q,rank,head_dim,s_cap,shared", [
     (2, 32, 64, 128, 300, True), (16, 32, 64, 128, 300, True), (8, 40, 64, 128, 500, True),
-    (8, 40, 64, 128, 700, False),   # 264 workgroups of the shared kernel
+    (8, 40, 64, 128, 700, True),    # ten splits: eleven would be 264 workgroups
+    (200, 40, 64, 128, 700, False),  # more than one round of the shared kernel's workgroups
     (8, 32, 16, 128, 2047, False), (8, 32, 16, 128, 2048, True), (8, 32, 64, 64, 300, False),
 ])
 def test_short_shared_base_form(batch, n_q, rank, head_dim, s_cap, shared):
@@ -493,7 +498,8 @@ def test_short_shared_base_form(batch, n_q, rank, head_dim, s_cap, shared):
 
     def splits(target, wgs):
         ns = max(1, min(-(-target // wgs), tiles))
-        return -(-tiles // -(-tiles // ns))
+        ns = -(-tiles // -(-tiles // ns))
+        return target // wgs if ns * wgs > target >= wgs else ns
     nw = 4 if rank == 64 else 8
     one, own = splits(256, groups), splits(256 * 8 // nw, batch * (8 // nw))
     part = batch * n_q * (4 + head_dim + rank) * 4

@@ -17,6 +17,8 @@ CASES = [
     ("decode_edges", 128, 16, 8, 2, 1, [1, 31, 32, 33, 2049, 4096], 8192, "kv", "own"),
     ("decode_one_of_many_tiles", 128, 16, 32, 8, 1, [1500], 32768, "kv", "own"),
     ("decode_r64", 128, 64, 10, 2, 1, [700, 65], 8192, "kv", "own"),
+    # 21 splits over up to 22 tiles: one or two tiles each.
+    ("decode_one_round", 128, 8, 8, 8, 1, [704, 703, 673, 672, 641, 1, 32, 33, 350, 700, 64, 65], 704, "kv", "own"),
     ("decode_d64_r8", 64, 8, 4, 4, 1, [333], 16384, "v", "own"),
     ("decode_paged_r64", 128, 64, 10, 2, 1, [700, 65, 2048], 8192, "kv", "paged"),
     ("decode_shared_two_groups", 128, 16, 8, 2, 1, [900, 33, 1, 64, 65, 31, 899, 5, 700], 8192, "kv", "shared"),
