@@ -859,9 +859,23 @@ lrsa_merge_kernel(const AttnArgs a) {
 // reads at its start and the combine at its end, is paid twice).
 constexpr int SH_W = 8;                                           // waves per workgroup
 constexpr int sh_groups(int rank) { return rank >= 64 ? 1 : 2; }  // request groups per workgroup (B_k in LDS: 64 KB at most)
-// Requests whose heads share the 16 columns; more than 4 would only lengthen
-// the per-request part of a sub-block.
-constexpr int sh_rpb(int group) { return group <= 4 ? 4 : (group == 5 ? 3 : 2); }
+// Requests whose heads share the 16 columns: what fits, but at most 4 (more
+// would only lengthen the per-request part of a sub-block), and no more than it
+// takes for as few workgroups: the empty slots of a last one cost the others
+// their time (8 requests, group 5, 14123 tokens, two workgroups of two groups of 3
+// / 2: rank 16 47.3 / 40.2 us, values only 34.7 / 32.2; 6 of 32768, group 4, one
+// workgroup of two groups of 4 / 3: 60.7 / 53.6).
+constexpr int sh_rpb_most(int group) { return group <= 4 ? 4 : (group == 5 ? 3 : 2); }
+inline int sh_rpb(int64_t batch, int group, int rank) {
+  const int most = sh_rpb_most(group);
+  const auto wgs = [&](int rpb) {
+    const int64_t rq = rpb * (batch > rpb ? sh_groups(rank) : 1);
+    return (batch + rq - 1) / rq;
+  };
+  for (int r = batch < most ? (int)batch : 2; r < most; ++r)
+    if (wgs(r) == wgs(most) && (batch > most || batch <= r)) return r;
+  return most;
+}
 
 template <int D, int R, int RPB>
 __global__ void __launch_bounds__(SH_W * 64, 2)
@@ -1412,7 +1426,7 @@ hipError_t launch_shared_rpb(AttnArgs a, hipStream_t st) {
 
 template <int D, int R>
 hipError_t launch_shared_t(const AttnArgs& a, hipStream_t st) {
-  switch (sh_rpb(a.group)) {
+  switch (sh_rpb(a.batch, a.group, R)) {
     case 4: return launch_shared_rpb<D, R, 4>(a, st);
     case 3: return launch_shared_rpb<D, R, 3>(a, st);
     default: return launch_shared_rpb<D, R, 2>(a, st);
@@ -1447,7 +1461,8 @@ int decode_tile_tokens() { return TK; }
 
 // Workgroups of the shared-base kernel for one split.
 static int64_t shared_workgroups(int64_t batch, int n_kv, int group, int rank) {
-  const int64_t rq = sh_rpb(group) * (batch > sh_rpb(group) ? sh_groups(rank) : 1);
+  const int rpb = sh_rpb(batch, group, rank);
+  const int64_t rq = rpb * (batch > rpb ? sh_groups(rank) : 1);
   return (int64_t)n_kv * ((batch + rq - 1) / rq);
 }
 

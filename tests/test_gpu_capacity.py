@@ -28,6 +28,9 @@ CASES = [
     ("decode_shared_g5_r64", 128, 64, 10, 2, 1, [200, 17, 16, 15, 1, 199, 64], 2048, "kv", "shared"),
     ("decode_shared_g8_r16", 128, 16, 16, 2, 1, [300, 31, 33, 299, 16], 2080, "kv", "shared"),
     ("decode_shared_g1_d64_r8", 64, 8, 2, 2, 1, [130, 129, 1, 16, 15, 64, 65, 100, 128], 2049, "kv", "shared"),
+    # Two full groups of 4, and of 2 with three of them over two workgroups.
+    ("decode_shared_eight", 128, 16, 8, 2, 1, [300, 299, 17, 1, 64, 33, 200, 16], 2048, "kv", "shared"),
+    ("decode_shared_g5_seven", 128, 8, 10, 2, 1, [310, 32, 17, 1, 64, 33, 200], 2048, "v", "shared"),
     ("decode_shared_short", 128, 16, 8, 2, 1, [130, 129, 1, 33], 2047, "kv", "shared"),  # each request by itself
     ("decode_shared_g3_qv_r32", 128, 32, 6, 2, 1, [500, 480, 17], 2500, "v", "shared"),
     ("prefill_split", 128, 16, 8, 2, 40, [300, 64, 65], 8192, "kv", "own"),

@@ -11,12 +11,14 @@ from workload import attention_case
 
 pytestmark = pytest.mark.gpu
 
-# d, r, n_q, n_kv, kv_lens: 4, 3 and 2 requests per result, one and two groups
-# per workgroup, L_v tiles of their own (ranks 8, 16) and in turn (32, 64).
+# d, r, n_q, n_kv, kv_lens: 3 + 2, 2 + 2, 2 + 1, 4 + 3 and 3 requests per result,
+# one and two groups per workgroup, L_v tiles of their own (ranks 8, 16) and in
+# turn (32, 64).
 CASES = [
     (128, 16, 8, 2, [2000, 700, 33, 1500, 90]),
     (128, 64, 10, 2, [1900, 40, 600, 1200]),
     (64, 8, 16, 2, [1000, 20, 900]),
+    (128, 16, 8, 2, [2000, 700, 33, 1500, 90, 1200, 1]),
     (128, 32, 6, 2, [2100, 64, 65]),
 ]
 
@@ -39,7 +41,7 @@ def _run(cfg, g):
 
 
 @pytest.mark.parametrize("name", ["L_v", "L_k"])
-@pytest.mark.parametrize("case", CASES, ids=lambda c: f"d{c[0]}r{c[1]}g{c[2] // c[3]}")
+@pytest.mark.parametrize("case", CASES, ids=lambda c: f"d{c[0]}r{c[1]}g{c[2] // c[3]}b{len(c[4])}")
 def test_one_agents_rows_stay_its_own(case, name):
     print(f"isolation {name} {case}", flush=True)
     cfg, g = _case(case)
@@ -55,7 +57,7 @@ def test_one_agents_rows_stay_its_own(case, name):
         assert torch.equal(Op[rest], O[rest]) and torch.equal(lp[rest], lse[rest])
 
 
-@pytest.mark.parametrize("case", CASES, ids=lambda c: f"d{c[0]}r{c[1]}g{c[2] // c[3]}")
+@pytest.mark.parametrize("case", CASES, ids=lambda c: f"d{c[0]}r{c[1]}g{c[2] // c[3]}b{len(c[4])}")
 def test_base_rows_of_the_longest_request_alone(case):
     """Base rows that only the longest request sees (a 16-token sub-block and
     more past the others' ends)."""
