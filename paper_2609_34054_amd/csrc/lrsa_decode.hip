@@ -68,6 +68,15 @@ constexpr int dec_prefetch(int rank) { return rank >= 64 ? 2 : 1; }
 // of 3000: 43.8 -> 34.0 us.
 constexpr bool dec_vdma(int d, int rank, bool staged) { return d == 128 && rank == 64 && !staged; }
 constexpr int dec_nw(int d, int rank, bool staged) { return dec_vdma(d, rank, staged) ? 8 : dec_waves(rank); }
+// Waves per SIMD the kernel is compiled for: two, except the register-staged
+// rank-64 form at d = 128, which takes the whole register file for one.  At d =
+// 64 it needs 256 registers, all of a wave's share at two: without the bound the
+// compiler took 258, and eleven paged requests of 30000 tokens, one KV head, 98 us
+// instead of 67.  (With several query tokens it needs more, and plans one
+// workgroup per CU.)
+constexpr int dec_occ(int d, int rank, bool staged, bool mt) {
+  return rank >= 64 && (d == 128 || mt) && !dec_vdma(d, rank, staged) ? 1 : 2;
+}
 constexpr int kLdsBlocks = 2048;  // block-table entries of a split the direct paged form holds in LDS
 constexpr int gcd_c(int a, int b) { return b == 0 ? a : gcd_c(b, a % b); }
 
@@ -355,7 +364,7 @@ constexpr int kStageLoads = D / 32 + Ex<R>::NC + RCH(R) + Dec<D, R>::NVD;
 // (It always takes the register-staged form, so that contiguous and paged
 // calls cut the same splits and agree bit for bit.)
 template <int D, int R, bool PAGED, bool MT, bool STAGED = PAGED || MT>
-__global__ void __launch_bounds__(dec_nw(D, R, STAGED) * 64, dec_nw(D, R, STAGED) / 4)
+__global__ void __launch_bounds__(dec_nw(D, R, STAGED) * 64, dec_occ(D, R, STAGED, MT))
 lrsa_decode_kernel(const AttnArgs a) {
   constexpr bool VD = dec_vdma(D, R, STAGED);
   constexpr bool LW = PAGED && VD;  // the table walk reads LDS
