@@ -486,12 +486,16 @@ size_t workspace_size(const lrsa_dims* dims, bool paged, bool optional = true) {
   }
   int n_splits = 0;
   // Paged caches always take the per-request decode kernel (requests may share
-  // some blocks and not others); the size covers either of its forms (the
-  // register-staged one has at least as many splits).
+  // some blocks and not others); the size covers either of its forms.
   const int cus = plan_cus(), group = dims->n_q_heads / dims->n_kv_heads;
   const bool shared = !paged && prc::decode_shares_base(dims->s_cap, dims->batch, dims->kv_req_stride, dims->n_kv_heads, group,
                                                         dims->head_dim, r, cus);
   prc::decode_plan(dims->s_cap, dims->batch, dims->n_kv_heads, group, dims->head_dim, r, shared, paged, cus, &n_splits);
+  if (paged) {
+    int direct = 0;
+    prc::decode_plan(dims->s_cap, dims->batch, dims->n_kv_heads, group, dims->head_dim, r, false, false, cus, &direct);
+    if (direct > n_splits) n_splits = direct;
+  }
   if (optional) {
     // Room for splits balanced over the requests (paged: in the form with the
     // longer splits, which it takes unless its block tables are very long).
