@@ -329,8 +329,8 @@ typedef struct lrsa_paging {
  * contents and no less than the recommended workspace, except where the two
  * take different kernels and sum in another order: a decode over a base that
  * contiguous requests share, a rank-64 decode (d = 128) whose tables have more
- * than 2048 entries a request or whose splits are one 32-token tile, and a
- * contiguous prefill that uses the tile cache.
+ * than 2048 entries a request, whose KV heads do not fill workgroups of eight or
+ * whose splits are short, and a contiguous prefill that uses the tile cache.
  *
  *   K_pool, V_pool  [n_kv_blocks, block_size, n_kv, d] bf16; request b's pool
  *              starts kv_req_stride * b elements in (normally 0: one pool

@@ -59,8 +59,8 @@ constexpr int dec_prefetch(int rank) { return rank >= 64 ? 2 : 1; }
 // loads, which frees the registers the V stages take: with one sub-block in
 // flight it then fits in 256 registers (251), so it runs 8-wave workgroups,
 // two waves per SIMD, like the lower ranks (64k, 8 requests: 467 -> 440 us).
-// Paged calls take it too while their block tables are short enough for the
-// split's entries to wait in LDS (a table read from memory between the stages
+// Paged calls take it too where it pays (decode_direct_paged) while their block
+// tables are short enough for the split's entries to wait in LDS (a table read from memory between the stages
 // would upset the fixed load count of the V wait below); longer tables, and
 // several query tokens, keep the register-staged 4-wave form (`staged`).
 // Eight paged requests of 65.5k tokens: 462 -> 426 us; of 36.8k-65.5k: 369 us,
@@ -1369,14 +1369,19 @@ __global__ void __launch_bounds__(64 * MR_ROWS) lrsa_merge_rows_kernel(const Att
 template <int D, int R>
 hipError_t launch_merge_t(const AttnArgs& a, hipStream_t st) {
   const int64_t n_rows = (int64_t)a.batch * a.n_tok * a.n_q;
-  // Chunks and shared-base calls of few rows take a workgroup per row with few
-  // splits too: one wave's reads of B_v and of the splits are a chain as long as
+  // Chunks, shared-base calls and paged rank-64 ones of few rows take a workgroup
+  // per row with few splits too: one wave's reads of B_v and of the splits are a chain as long as
   // the rank, and too few rows run side by side to hide it (4 tokens of 4
   // requests over 512 keys, dim 128, one wave / four: rank 16 19.9 / 15.7 us, 32
   // 23.5 / 18.5; 8 requests over one base, rank 64, of 500 tokens 26.2 / 20.5,
-  // of 64, two splits, 20.7 / 18.3).  Not more rows: 100 requests, 1600 rows of 5
+  // of 64, two splits, 20.7 / 18.3; 8 paged requests of 2048 tokens, rank 64, 41.7
+  // / 30.0).  Not more rows: 100 requests, 1600 rows of 5
   // splits 11.0 / 12.1; 2560 rows of 6 splits, rank 64, 23.9 / 26.7.
-  const bool few_rows = a.dec_group != 0 && (a.n_tok > 1 || a.dec_shared) && n_rows <= (a.n_splits >= 8 ? 2048 : 1024);
+  // (Paged: the register-staged form at d = 128 only; the others are to sum as the
+  // contiguous calls do.)
+  const bool staged64 = D == 128 && R == 64 && a.kv_tbl != nullptr && !a.dec_direct;
+  const bool few_rows = a.dec_group != 0 && (a.n_tok > 1 || a.dec_shared || staged64) &&
+                        n_rows <= (a.n_splits >= 8 ? 2048 : 1024);
   if (a.n_splits <= 16 && !few_rows) {
     hipLaunchKernelGGL((lrsa_merge_rows_kernel<D, R>), dim3((unsigned)((n_rows + MR_ROWS - 1) / MR_ROWS)),
                        dim3(64 * MR_ROWS), 0, st, a, n_rows);
@@ -1559,41 +1564,47 @@ void decode_plan(int64_t s_cap, int batch, int n_kv, int group, int head_dim, in
   int64_t ns, st;
   plan(2, &ns, &st);
   if (st < 8 || shared_base || dec_vdma(head_dim, rank, staged)) plan(1, &ns, &st);
+  // The form that holds the whole register file runs one four-wave workgroup per
+  // CU, and one round of them: a second costs its start again, with or without
+  // keys (paged, rank 64, 8 KV heads, splits for two / one: one request of 5955 of
+  // 9024 tokens 24.5 / 21.3 us, five of 2256 of 9024 31.0 / 24.4).
+  if (staged && !shared_base && dec_occ(head_dim, rank, true, false) == 1 && groups <= cus && ns > cus / groups)
+    ns = cus / groups;
   *n_splits = (int)ns;
 }
 
-// A chunk's splits are a decode's in the register-staged form, but at rank 64
-// no more than one of its workgroups per CU: they hold the whole register file,
-// so further ones queue, and a context short for its cache pays a start of
-// several microseconds for each round of them whether they find keys or not.
-// (4 tokens of 6 requests, 32 / 8 heads of dim 128, 64 of 65920 tokens: 19.7 us
-// as a prefill, 30.3 with four rounds, 18.2 so; 8192 of 8192: 73, 81 and 56.)
+// A chunk's splits are a decode's in the register-staged form, at rank 64 one
+// workgroup per CU for either head dim.  (4 tokens of 6 requests, 32 / 8 heads of
+// dim 128, 64 of 65920 tokens: 19.7 us as a prefill, 30.3 with four rounds, 18.2
+// so; 8192 of 8192: 73, 81 and 56.)
 void decode_chunk_plan(int64_t s_cap, int batch, int n_kv, int group, int head_dim, int rank, int cus, int* n_splits) {
   decode_plan(s_cap, batch, n_kv, group, head_dim, rank, false, true, cus, n_splits);
-  if (rank < 64) return;
+  if (dec_occ(head_dim, rank, true, true) > 1) return;
   const int nw = dec_waves(rank);
   const int64_t tiles = (s_cap + TK - 1) / TK, groups = (int64_t)(batch > 0 ? batch : 1) * ((n_kv + nw - 1) / nw);
-  const int64_t most = cus / groups > 1 ? cus / groups : 1;
-  if (*n_splits <= most) return;
-  const int64_t st = (tiles + most - 1) / most;
+  const int64_t most = cus / groups > 1 ? cus / groups : 1, n = *n_splits < most ? *n_splits : most;
+  const int64_t st = (tiles + n - 1) / n;
   *n_splits = (int)((tiles + st - 1) / st);
 }
 
-// A paged rank-64 call takes the direct-V form where the register-staged one
-// would run splits of two tiles or more: at one tile there is nothing for the
-// extra waves to overlap with, and its longer start shows (1 request of 1024 /
-// 2048 tokens: 19.9 / 22.0 us staged, 24.9 / 25.8 direct; 3: 22.4 / 34.2 and
-// 26.1 / 26.8; 8: 35.2 / 41.6 and 28.0 / 33.7; 1 of 8192: 36.1 and 28.9).
-// The line is on the capacity; a short context in a large cache pays the direct
-// form's start, but not the staged form's rounds of workgroups without keys (1 /
-// 3 / 8 requests of 256 of 65920 tokens: 42.4 / 61.6 / 63.1 us staged, in splits
-// of the capacity, and 23.0 / 24.8 / 25.5).
+// A paged rank-64 call takes the direct-V form, eight KV heads a workgroup,
+// - where it leaves no more waves idle than the register-staged one, four heads a
+//   workgroup (30000 tokens, six / twenty requests, 4 KV heads: 98.8 / 288 us
+//   staged, 143 / 377 direct; 10 KV heads, six: 272 and 341), and
+// - where the staged splits would be longer than 24 tiles: shorter ones lose more
+//   by the direct form's longer start than its second wave per SIMD brings (8 KV
+//   heads, staged / direct: one request of 5955 of 9024 tokens 21.2 / 29.2 us,
+//   eight of 2048 of 2048 30.0 / 34.3, of 9024 of 9024 75.4 / 80.1; past it, eight
+//   of 10813, 10475, .. of 16384 86.9 / 85.4, of 16384 121.8 / 124.0; 24 and 32 are
+//   alike over 354 shapes, 64 is slower for some).
+// With more staged workgroups than CUs it is the direct form's one round against
+// two.  The line is on the capacity; the splits of both divide the keys in use.
 bool decode_direct_paged(int64_t s_cap, int batch, int n_tok, int n_kv, int head_dim, int rank, int max_blk, int cus) {
   if (!dec_vdma(head_dim, rank, false) || n_tok != 1 || max_blk > kLdsBlocks) return false;
-  const int nw = dec_nw(head_dim, rank, true);
-  const int64_t groups = (int64_t)batch * ((n_kv + nw - 1) / nw);
-  const int64_t ns = ((int64_t)(cus > 0 ? cus : 1) * 8 / nw + groups - 1) / groups;
-  return (s_cap + TK - 1) / TK > (ns < kMaxSplits ? ns : kMaxSplits);
+  const int nw = dec_nw(head_dim, rank, true), per_req = (n_kv + nw - 1) / nw;
+  if (per_req % 2) return false;
+  const int64_t tiles = (s_cap + TK - 1) / TK, groups = (int64_t)batch * per_req;
+  return groups > cus ? tiles > 2 : tiles > 24 * (cus / groups);
 }
 
 // A chunk of a few query tokens whose (token, head) pairs per KV head fit the
