@@ -31,7 +31,7 @@
 //      per-lane scalar.
 // The loads of the next sub-block (the next two in the 4-wave rank-64
 // kernel) are in flight while the current one is consumed.  The direct form of
-// the rank-64 kernel at d = 128 (contiguous calls and most paged ones, one query
+// the rank-64 kernel at d = 128 (contiguous calls and long paged ones, one query
 // token) sends its V rows straight to LDS (direct global->LDS loads into a
 // two-buffer ring) instead of through registers.
 #include "common.hpp"
@@ -60,9 +60,10 @@ constexpr int dec_prefetch(int rank) { return rank >= 64 ? 2 : 1; }
 // flight it then fits in 256 registers (251), so it runs 8-wave workgroups,
 // two waves per SIMD, like the lower ranks (64k, 8 requests: 467 -> 440 us).
 // Paged calls take it too where it pays (decode_direct_paged) while their block
-// tables are short enough for the split's entries to wait in LDS (a table read from memory between the stages
-// would upset the fixed load count of the V wait below); longer tables, and
-// several query tokens, keep the register-staged 4-wave form (`staged`).
+// tables are short enough for the split's entries to wait in LDS (a table read
+// from memory between the stages would upset the fixed load count of the V wait
+// below); the others, and several query tokens, keep the register-staged 4-wave
+// form (`staged`).
 // Eight paged requests of 65.5k tokens: 462 -> 426 us; of 36.8k-65.5k: 369 us,
 // 410 with equal splits for each request, 345 with balanced ones (below); four
 // of 3000: 43.8 -> 34.0 us.
