@@ -1152,8 +1152,13 @@ void prefill_plan(int n_tok, int group, int n_kv, int batch, int64_t s_cap, int 
   // With more units than CUs a split only evens out the last round, and its
   // partials cost as much as many tiles: short contexts in a large cache then
   // take fewer of the planned splits (3 requests, 1554 queries over 1777 of
-  // 7108 tokens, rank 8, planned 5 ways: 835 us in fifths, 630 so).
-  if (min_tiles != nullptr && units > n_cu) *min_tiles = (int)(st < 32 ? st : 32);
+  // 7108 tokens, rank 8, planned 5 ways: 835 us in fifths, 630 so).  Splits over
+  // several rounds of the CUs start that often, so they keep to a few tiles too
+  // (700 queries over 1700 of 4700 tokens, 64 / 8 heads, rank 16, 1232 workgroups
+  // planned: 166 us with splits of the capacity, 232 in sevenths of the keys, 158
+  // in splits of at least 12 tiles).  One round has nothing to start again.
+  const int64_t least = units > n_cu ? 32 : (units * *splits > 3 * n_cu ? 12 : (units * *splits > 2 * n_cu ? 8 : 1));
+  if (min_tiles != nullptr) *min_tiles = (int)(st < least ? st : least);
 }
 
 size_t prefill_workspace_bytes(int batch, int n_tok, int n_q, int splits, int head_dim, int rank) {
